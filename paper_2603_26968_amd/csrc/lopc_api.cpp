@@ -361,7 +361,6 @@ int lopc_compress(lopc_ctx* ctx, const void* d_field, int dtype, int ndim,
   const uint64_t k = dtype == 0 ? 4 : 8, W = kChunkBytes / k;
   const uint64_t nch = (s.n + W - 1) / W;
   Tiling tl = make_tiling(s.box, ctx->tile2, ctx->tile3);
-  if (s.box.nz == 1) tl.lev = ws + L.lev;
   tl.coloured = ctx->sweep_order == 1 || (ctx->sweep_order == 0 && tl.ntiles >= kColourMinTiles);
   const int rmode = ctx->repair_mode;
   QueueRef Q{};

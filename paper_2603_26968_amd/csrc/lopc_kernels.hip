@@ -15,7 +15,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "lopc_device.h"
+#include "lopc_tile.h"
 
 namespace lopc {
 namespace {
@@ -172,31 +172,6 @@ __global__ __launch_bounds__(kThreads) void k_params(
 // and, if a boundary value changed, marks the 26 neighbour tiles for the next
 // sweep.  Sweeps repeat until no tile is marked; the result is the least
 // fixed point whatever the order in which tiles run.
-template <int TZ, int TY, int TX>
-struct TileGeom {
-  static constexpr int ZO = TZ == 1 ? 0 : 1;  // 2D tiles carry no z halo
-  static constexpr int HZ = TZ + 2 * ZO, HY = TY + 2, HX = TX + 2;
-  static constexpr int H = HZ * HY * HX;
-  static constexpr int NPT = TZ * TY * TX;
-  static constexpr int PER = NPT / kThreads;
-  static_assert(NPT % kThreads == 0, "tile must be a multiple of the block");
-  // owned point tid + k * kThreads (slot k of thread tid) lies kSlot LDS
-  // words after slot 0: the block covers whole planes of a 3D tile, or whole
-  // rows of a 2D one
-  static_assert((TZ > 1 && TY * TX == kThreads) || (TZ == 1 && kThreads % TX == 0),
-                "slots of a thread are evenly spaced in LDS");
-  static constexpr int kSlot = TZ > 1 ? HY * HX : (kThreads / TX) * HX;
-  // halo-local index of interior point i
-  __device__ static int local(int i) {
-    int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-    return ((iz + ZO) * HY + iy + 1) * HX + ix + 1;
-  }
-  __device__ static bool on_edge(int i) {
-    int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-    return (TZ > 1 && (iz == 0 || iz == TZ - 1)) || iy == 0 || iy == TY - 1 ||
-           ix == 0 || ix == TX - 1;
-  }
-};
 
 // Neighbour tiles reached from owned point i along the stencil offsets in
 // `bits` (a subset of the point's 14 / 6 offsets), as a 27-bit set: bit
@@ -356,10 +331,23 @@ __device__ __forceinline__ uint32_t dense_best(const uint32_t* S, int li, uint32
   return r;
 }
 
+// ---------------------------------------------------------------- LDS words
+// A tile run keeps one 32-bit word per halo point in LDS: the subbin in the
+// low half, the point's order flags inverted in bits 16..29 (bit 16 + j clear:
+// the neighbour at stencil offset j is a same-bin lower neighbour; points
+// outside the tile in the first pass, and points outside the grid, have them
+// all set), kRose once the run has raised it, kHalo if it lies outside the
+// tile.  So one LDS read of a neighbour gives both its subbin and whether it
+// depends on the point that reads it, and the maximum of two words of one
+// point is the word of its larger subbin.  Subbins above kPackMax go the
+// 32-bit way (relax_wide): a run raises a point by at most the points of its
+// tile, so 16 bits suffice below it.
+constexpr uint32_t kRose = 1u << 30, kNoFlags = 0x3fffu << 16;  // kHalo: 1 << 31
+constexpr uint32_t kPackMax = 60000;
+
 // Mask bits j of a point's flags spread over bytes: byte b of word r is
 // 0xff when bit 4r + b is set, so that an SDWA operand sign-extends byte b
-// to the all-ones / zero word dense_best builds with one instruction per
-// neighbour.
+// to the all-ones / zero word that masks a neighbour's subbin.
 template <int NW>
 __device__ __forceinline__ void spread_mask(uint32_t m, uint32_t (&pk)[NW]) {
 #pragma unroll
@@ -369,127 +357,341 @@ __device__ __forceinline__ void spread_mask(uint32_t m, uint32_t (&pk)[NW]) {
     pk[r] = (y << 8) - y;                                  // 0x01 -> 0xff
   }
 }
-// v & sext(byte B of p), and (v & sext(byte B of p)) - sext(byte B of p)
+// the subbin of word v & sext(byte B of p)
 template <int B>
 __device__ __forceinline__ uint32_t and_sext(uint32_t v, uint32_t p) {
   uint32_t r;
   if constexpr (B == 0)
-    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(v), "v"(p));
+    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:BYTE_0" : "=v"(r) : "v"(v), "v"(p));
   else if constexpr (B == 1)
-    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(v), "v"(p));
+    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:BYTE_1" : "=v"(r) : "v"(v), "v"(p));
   else if constexpr (B == 2)
-    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(v), "v"(p));
+    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:BYTE_2" : "=v"(r) : "v"(v), "v"(p));
   else
-    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(v), "v"(p));
+    asm("v_and_b32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:BYTE_3" : "=v"(r) : "v"(v), "v"(p));
   return r;
 }
-template <int B>
-__device__ __forceinline__ uint32_t sub_sext(uint32_t v, uint32_t p) {
+// the subbin of word v & mask w
+__device__ __forceinline__ uint32_t and_word(uint32_t v, uint32_t w) {
   uint32_t r;
-  if constexpr (B == 0)
-    asm("v_sub_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(v), "v"(p));
-  else if constexpr (B == 1)
-    asm("v_sub_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(v), "v"(p));
-  else if constexpr (B == 2)
-    asm("v_sub_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(v), "v"(p));
-  else
-    asm("v_sub_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(v), "v"(p));
+  asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:DWORD" : "=v"(r) : "v"(v), "v"(w));
   return r;
 }
-// the masked candidates of neighbours J.. (J a compile-time constant)
+// the masked subbins of neighbours J.. (J a compile-time constant)
 template <int J, int NJ, int HX, int HXY, int NW>
-__device__ __forceinline__ void pk_cands(const uint32_t* S, int li, const uint32_t (&pk)[NW],
+__device__ __forceinline__ void pk_cands(const uint32_t* P, int li, const uint32_t (&pk)[NW],
                                          uint32_t* c) {
   if constexpr (J < NJ) {
-    const uint32_t v = S[li + kOff[J][0] * HXY + kOff[J][1] * HX + kOff[J][2]];
-    const uint32_t vw = and_sext<J & 3>(v, pk[J >> 2]);
-    if constexpr (J & 1) c[J] = vw;
-    else c[J] = sub_sext<J & 3>(vw, pk[J >> 2]);
-    pk_cands<J + 1, NJ, HX, HXY, NW>(S, li, pk, c);
+    const uint32_t v = P[li + kOff[J][0] * HXY + kOff[J][1] * HX + kOff[J][2]];
+    c[J] = and_sext<J & 3>(v, pk[J >> 2]);
+    pk_cands<J + 1, NJ, HX, HXY, NW>(P, li, pk, c);
   }
 }
-// dense_best with the mask spread over bytes (spread_mask)
-template <int NJ, int HX, int HXY, int NW>
-__device__ __forceinline__ uint32_t dense_best_pk(const uint32_t* S, int li, const uint32_t (&pk)[NW],
-                                                  uint32_t cur) {
-  uint32_t c[NJ];
-  pk_cands<0, NJ, HX, HXY, NW>(S, li, pk, c);
-  uint32_t a = max(max(cur, c[0]), c[1]);
-  uint32_t b = max(max(c[2], c[3]), c[4]);
-  uint32_t r = max(max(a, b), c[5]);
+// The larger of cur and the best raise from masked neighbours c (0 where the
+// flag is clear): the neighbours of higher index (even j) weigh 1, added once
+// to their maximum if any of them is flagged.
+template <int NJ>
+__device__ __forceinline__ uint32_t fold_cands(const uint32_t* c, uint32_t m, uint32_t cur) {
+  const uint32_t up = min(m & (NJ > 6 ? 0x1555u : 0x15u), 1u);
+  uint32_t e = max(max(c[0], c[2]), c[4]), o = max(max(c[1], c[3]), c[5]);
   if constexpr (NJ > 6) {
-    const uint32_t d = max(max(c[6], c[7]), c[8]);
-    const uint32_t e = max(max(c[9], c[10]), c[11]);
-    const uint32_t f = max(max(c[12], c[13]), d);
-    r = max(max(r, e), f);
+    e = max(max(e, c[6]), c[8]);
+    e = max(max(e, c[10]), c[12]);
+    o = max(max(o, c[7]), c[9]);
+    o = max(max(o, c[11]), c[13]);
+  }
+  return max(max(cur, o), e + up);
+}
+// The best raise of the point at LDS index li with lower-neighbour mask m
+// from the words of all its stencil neighbours, one masking instruction per
+// neighbour where the mask is spread (pk).
+template <int NJ, int HX, int HXY, int NW>
+__device__ __forceinline__ uint32_t pull_best_pk(const uint32_t* P, int li, uint32_t m,
+                                                 const uint32_t (&pk)[NW], uint32_t cur) {
+  uint32_t c[NJ];
+  pk_cands<0, NJ, HX, HXY, NW>(P, li, pk, c);
+  return fold_cands<NJ>(c, m, cur);
+}
+template <int NJ, int HX, int HXY>
+__device__ __forceinline__ uint32_t pull_best(const uint32_t* P, int li, uint32_t m,
+                                              uint32_t cur) {
+  uint32_t c[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const uint32_t v = P[li + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]];
+    c[j] = and_word(v, (uint32_t)((int32_t)(m << (31 - j)) >> 31));
+  }
+  return fold_cands<NJ>(c, m, cur);
+}
+
+// A pass of the first run that raises at most this many of a tile's NPT points
+// hands over to event rounds.
+template <int NPT>
+constexpr uint32_t kEventShare = NPT / 16;
+// Events of a round up to which each gets a lane per neighbour.
+constexpr uint32_t kNarrow = 32;
+
+// Event lists of a tile run (LDS indices of raised points; two alternating
+// lists per wave) and its block-wide words.
+template <int NPT>
+struct EventLds {
+  static constexpr uint32_t kCap = NPT / kWaves;  // entries of one list: a wave's slots
+  uint16_t list[kWaves][2][kCap];
+  uint32_t over;     // a list was full: points were not listed
+  uint32_t big;      // a loaded subbin exceeds kPackMax
+  uint32_t dirs;     // neighbour tiles to mark (27-direction set)
+  uint32_t rose[3];  // points raised by pass p in slot p % 3
+};
+
+// Append the lanes' points (where `go`) to one of the wave's lists of n
+// entries (wave-uniform; slots of a wave always fit).
+__device__ __forceinline__ void list_points(uint16_t* list, uint32_t& n, bool go, int li) {
+  const uint64_t b = __ballot(go);
+  if (go) list[n + lane_prefix(b)] = (uint16_t)li;
+  n += (uint32_t)__popcll(b);
+}
+
+// An LDS word rises to subbin nv where `hit` (q: the word as read); returns
+// the word before, ~0 where not.  The maximum of the words keeps the larger
+// subbin: their flags agree, and a word without kRose has not changed since it
+// was read.
+__device__ __forceinline__ uint32_t raise_word(uint32_t* w, bool hit, uint32_t q, uint32_t nv) {
+  uint32_t old = ~0u;
+  if (hit)
+    old = __hip_atomic_fetch_max(w, (q & 0xffff0000u) | kRose | nv, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+  return old;
+}
+
+// The points that rose to nv (old: the word before) and lie in the tile join
+// the wave's list of n entries; a full list sets E.over.
+template <int NPT>
+__device__ __forceinline__ void list_risen(EventLds<NPT>& E, uint16_t* list, uint32_t& n,
+                                           uint32_t old, int li, uint32_t nv) {
+  const bool up = (old & (0xffffu | kHalo)) < nv;
+  const uint64_t b = __ballot(up);
+  if (!b) return;
+  const uint32_t c = (uint32_t)__popcll(b);
+  if (n + c > EventLds<NPT>::kCap) {
+    E.over = 1;
+    return;
+  }
+  if (up) list[n + lane_prefix(b)] = (uint16_t)li;
+  n += c;
+}
+
+// Event rounds of one wave, from the n points of its list[0]: every listed
+// point pushes its subbin to its stencil neighbours that depend on it, and
+// those that rise push in turn until none does.  A round costs its events, not
+// the points of the tile: in a later run about one point in twenty rises from
+// the halo, and fewer in every round after.  A wave keeps the points it raises
+// in lists of its own, so the waves need no barriers (a point raised by one
+// while another pushes it is pushed again by the one that raised it).  All
+// words of a round are read at once (one LDS round trip), then the raises are
+// LDS maxima issued together.  Rounds of few events give each event a lane per
+// neighbour instead of a lane in all.  Halo words rise too (kRose marks them),
+// but push nothing.  A point raised twice in a round is listed twice (its
+// second event finds nothing to raise).  Returns the rounds.
+// Bound by vector issue on large fields and by the latency of the rounds on
+// small ones.  Against passes over all points until none rises: the 24 sweep
+// launches on a 512^3 float64 lognormal field 8.3 -> 6.1 ms (vector
+// instructions of the first 2971 -> 1790 per wave, of the sixth 1298 -> 550),
+// 2D 1800 x 3600 float32 sweeps 304 -> 190 us.
+template <int TZ, int TY, int TX>
+__device__ __forceinline__ int push_rounds(uint32_t* P, EventLds<TZ * TY * TX>& E, uint32_t n) {
+  using G = TileGeom<TZ, TY, TX>;
+  constexpr int NJ = TZ == 1 ? 6 : 14;
+  constexpr int HX = G::HX, HXY = G::HY * G::HX;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane(wave());
+  // narrow rounds: kPer lanes to an event, one neighbour each
+  constexpr int kPer = NJ == 6 ? 8 : 16, kPerWave = 64 / kPer;
+  const int jl = lane() % kPer;
+  const int offl = jl < NJ ? off_lin(jl, HX, HXY) : 0;
+  const uint32_t keepl = 0xffffu | 1u << (16 + ((jl < NJ ? jl : 0) ^ 1));
+  int r = 0;
+  while (n) {
+    const uint16_t* in = E.list[w][r & 1];
+    uint16_t* out = E.list[w][(r + 1) & 1];
+    uint32_t made = 0;
+    auto narrow = [&](auto U_, uint32_t b) {
+      constexpr int U = decltype(U_)::value;
+      int l[U];
+      uint32_t v[U], q[U], old[U];
+      bool act[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t e = b + (uint32_t)(u * kPerWave + lane() / kPer);
+        act[u] = e < n && jl < NJ;
+        l[u] = act[u] ? (int)in[e] : G::local(0);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = P[l[u]];
+        l[u] += offl;
+        q[u] = P[l[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v[u] = act[u] ? (v[u] & 0xffffu) + (uint32_t)(jl & 1) : 0u;
+        old[u] = raise_word(&P[l[u]], (q[u] & keepl) < v[u], q[u], v[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) list_risen(E, out, made, old[u], l[u], v[u]);
+    };
+    if (n <= kPerWave) {
+      narrow(std::integral_constant<int, 1>{}, 0u);
+    } else if (n <= kNarrow) {
+      for (uint32_t b = 0; b < n; b += 4 * kPerWave) narrow(std::integral_constant<int, 4>{}, b);
+    } else {
+      for (uint32_t b = 0; b < n; b += 64) {
+        const bool act = b + (uint32_t)lane() < n;
+        const int p = act ? (int)in[b + lane()] : G::local(0);
+        const uint32_t v = P[p] & 0xffffu;
+        uint32_t q[NJ], old[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          q[j] = P[p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]];
+        // neighbour j sees p at offset j ^ 1, with weight 1 for odd j (p has
+        // the higher index): a hit if its flag bit is clear and its subbin is
+        // lower
+        const uint32_t nv[2] = {act ? v : 0u, act ? v + 1 : 0u};
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          old[j] = raise_word(&P[p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]],
+                              (q[j] & (0xffffu | 1u << (16 + (j ^ 1)))) < nv[j & 1], q[j],
+                              nv[j & 1]);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          list_risen(E, out, made, old[j], p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2],
+                     nv[j & 1]);
+      }
+    }
+    n = made;
+    ++r;
+    __builtin_amdgcn_wave_barrier();
   }
   return r;
 }
 
-// Local fixed point of the tile (masks of the owned points in registers):
-// Gauss-Seidel passes over the owned points until none rises; the halo is
-// fixed.  Only points with a same-bin lower neighbour can rise; in a 3D
-// tile whose wave holds at most 64 of them over its slots, the wave first
-// gathers them into one lane each (a per-wave list in LDS), so that a pass
-// costs one step per wave instead of one per slot, and each listed point
-// with at most three lower neighbours reads them at precomputed offsets
-// (walk_code: three loads issued back to back).  Otherwise a pass visits the
-// slots and walks the mask bits.  When some lane of the wave has more than
-// three lower neighbours, the wave loads all stencil neighbours and selects
-// under the mask.  Adds the pass count to one of 64 statistics slots
-// itot[t % 64].  PK (3D tiles): the slots' masks are spread over bytes once
-// (spread_mask) and the dense visit masks with one SDWA instruction per
-// neighbour: fewer vector instructions, 16 more registers (used by the
-// float64 first pass and the repair of four-slot tiles; the float32 first
-// pass loses more occupancy than it saves).
-template <int TZ, int TY, int TX, bool PK = false>
-__device__ void relax(uint32_t* S, const uint16_t* mk, uint32_t* counters,
-                      unsigned long long* itot, uint32_t t) {
+// One pass over the owned points, flags and subbins from the LDS words, slots
+// in ascending or descending order; returns the slots that rose (bit k).
+template <int TZ, int TY, int TX>
+__device__ __forceinline__ uint32_t word_pass(uint32_t* P, bool rev) {
   using G = TileGeom<TZ, TY, TX>;
-  constexpr int NJ = TZ == 1 ? 6 : 14;  // 2D tiles: the in-plane offsets only
+  constexpr int NJ = TZ == 1 ? 6 : 14;
+  const int li0 = G::local(threadIdx.x);
+  uint32_t changed = 0;
+#pragma unroll 2
+  for (int kk = 0; kk < G::PER; ++kk) {
+    const int k = rev ? G::PER - 1 - kk : kk;
+    const int li = li0 + k * G::kSlot;
+    const uint32_t w = P[li], m = (~w >> 16) & (TZ == 1 ? 0x3fu : 0x3fffu), cur = w & 0xffffu;
+    if (!m) continue;
+    const uint32_t best = pull_best<NJ, G::HX, G::HY * G::HX>(P, li, m, cur);
+    if (best > cur) {
+      P[li] = (w + (best - cur)) | kRose;
+      changed |= 1u << k;
+    }
+  }
+  return changed;
+}
+
+// adds the points that rose (bit k of changed: slot k) to E.rose[slot]
+template <int PER, int NPT>
+__device__ __forceinline__ void count_rose(EventLds<NPT>& E, uint32_t changed, int slot) {
+  uint32_t rose = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) rose += (uint32_t)__popcll(__ballot((changed >> k) & 1u));
+  if (rose && lane() == 0) atomicAdd(&E.rose[slot], rose);
+}
+
+// Passes until no owned point rises (after a full event list).  Every thread
+// calls it past a block barrier; returns the passes.
+template <int TZ, int TY, int TX>
+__device__ __noinline__ int word_passes(uint32_t* P, EventLds<TZ * TY * TX>& E,
+                                        uint32_t* counters) {
+  using G = TileGeom<TZ, TY, TX>;
+  if (threadIdx.x < 3) E.rose[threadIdx.x] = 0;
+  __syncthreads();
+  int iters = 0;
+  for (;;) {
+    if (threadIdx.x == 0) E.rose[(iters + 1) % 3] = 0;
+    const uint32_t changed = word_pass<TZ, TY, TX>(P, iters & 1);
+    count_rose<G::PER>(E, changed, iters % 3);
+    __syncthreads();
+    if (!E.rose[iters % 3]) return iters + 1;
+    if (++iters > G::NPT + 2) {  // unreachable: the order inside a tile is acyclic
+      if (threadIdx.x == 0) atomicOr(&counters[0], 1u);
+      return iters;
+    }
+  }
+}
+
+// Local fixed point of a tile in the first pass: Gauss-Seidel passes over the
+// owned points, then event rounds; the halo is fixed.  Only points with a
+// same-bin lower neighbour can rise; a wave whose slots hold at most 64 of
+// them first gathers them into one lane each (a per-wave list in LDS), so that
+// a pass costs one step per wave instead of one per slot, and each listed
+// point with at most three lower neighbours reads them at precomputed offsets
+// (walk_code: three loads issued back to back).  Other waves visit their slots
+// and read every stencil neighbour at once, masked.  Once a pass raises at
+// most a quarter of the points (and some wave is not listed), those points
+// become the first event list.  On a lognormal field (91% of the points in
+// one bin) the passes raise 77, 54, 40, 31, 25, 19, 15, 12% ... of the points,
+// fifteen in all: the later ones cost far less as events.  Adds the pass count
+// to one of 64 statistics slots itot[t % 64].  PK: the slots' masks are spread
+// over bytes once (spread_mask) and a visit masks with one SDWA instruction
+// per neighbour: fewer vector instructions, 16 more registers (the float64
+// first pass; the float32 one loses more occupancy than it saves).
+template <int TZ, int TY, int TX, bool PK = false>
+__device__ void relax(uint32_t* P, EventLds<TZ * TY * TX>& E, const uint16_t* mk,
+                      uint32_t* counters, unsigned long long* itot, uint32_t t) {
+  using G = TileGeom<TZ, TY, TX>;
+  static_assert(TZ > 1, "2D tiles peel");
+  constexpr int NJ = 14;
   static_assert(G::H < 4096, "halo index in 12 bits");
-  __shared__ uint32_t wl_pt[kThreads], wl_cd[kThreads];  // wave w: entries [64w, 64w + 64)
+  // the candidates of a listed wave, in the room of its event lists (64 each)
+  const int w = __builtin_amdgcn_readfirstlane(wave());
+  uint32_t* wl_pt = (uint32_t*)&E.list[w][0][0];
+  static_assert(sizeof(E.list[0]) >= 256, "the candidates fit the event lists");
+  __shared__ uint32_t dense;  // some wave is not listed
   // a listed point: rise to the best of its lower neighbours (a positive
   // offset, even j, reaches a higher index and adds one)
   auto step = [&](int li, uint32_t m, uint32_t cd) -> bool {
-    const uint32_t cur = S[li];
+    const uint32_t w = P[li], cur = w & 0xffffu;
     uint32_t best = cur;
     if (__ballot(cd == kDense)) {
-      best = dense_best<NJ, G::HX, G::HY * G::HX>(S, li, m, cur);
+      best = pull_best<NJ, G::HX, G::HY * G::HX>(P, li, m, cur);
     } else {
       const int o0 = (int)(cd & 1023u) - 512, o1 = (int)((cd >> 10) & 1023u) - 512,
                 o2 = (int)((cd >> 20) & 1023u) - 512;
-      const uint32_t c0 = S[li + o0] + (o0 > 0), c1 = S[li + o1] + (o1 > 0),
-                     c2 = S[li + o2] + (o2 > 0);
+      const uint32_t c0 = (P[li + o0] & 0xffffu) + (o0 > 0), c1 = (P[li + o1] & 0xffffu) + (o1 > 0),
+                     c2 = (P[li + o2] & 0xffffu) + (o2 > 0);
       best = max(max(best, c0), max(c1, c2));
     }
     if (best > cur) {
-      S[li] = best;
+      P[li] = w + (best - cur);
       return true;
     }
     return false;
   };
-  // gather this wave's candidate points (3D tiles; in 2D fields same-bin
-  // neighbours are common and the lists rarely fit)
-  constexpr bool kList = TZ > 1;
-  constexpr int LP = kList ? G::PER : 1;
-  uint64_t act[LP];  // wave-uniform
-  uint32_t n = kList ? 0u : 65u;
+  // gather this wave's candidate points
+  uint64_t act[G::PER];  // wave-uniform
+  uint32_t n = 0;
 #pragma unroll
-  for (int k = 0; k < (kList ? G::PER : 0); ++k) {
+  for (int k = 0; k < G::PER; ++k) {
     act[k] = __ballot(mk[k] != 0);
     n += (uint32_t)__popcll(act[k]);
   }
   const bool listed = n <= 64;
-  if (kList && listed) {
+  if (listed) {
     uint32_t base = 0;
 #pragma unroll
-    for (int k = 0; k < LP; ++k) {
+    for (int k = 0; k < G::PER; ++k) {
       if (mk[k]) {
         const uint32_t pos = base + (uint32_t)__popcll(act[k] & ((1ull << lane()) - 1ull));
-        wl_pt[wave() * 64 + pos] =
+        wl_pt[pos] =
             (uint32_t)G::local(threadIdx.x + k * kThreads) | (uint32_t)mk[k] << 12;
-        wl_cd[wave() * 64 + pos] = walk_code<TZ, TY, TX>(mk[k]);
       }
       base += (uint32_t)__popcll(act[k]);
     }
@@ -497,48 +699,55 @@ __device__ void relax(uint32_t* S, const uint16_t* mk, uint32_t* counters,
   uint32_t my_pt = 0, my_cd = 0;
   __builtin_amdgcn_wave_barrier();
   if (listed && (uint32_t)lane() < n) {
-    my_pt = wl_pt[wave() * 64 + lane()];
-    my_cd = wl_cd[wave() * 64 + lane()];
+    my_pt = wl_pt[lane()];
+    my_cd = walk_code<TZ, TY, TX>(my_pt >> 12);
   }
   // slot k of this thread lies kSlot LDS words after slot 0
   const int li0 = G::local(threadIdx.x);
-  // whether any point rose in pass p: flag[p % 3], set by the waves that
-  // raised one, read by all after the pass's barrier; thread 0 clears
-  // flag[(p + 1) % 3] during pass p (last read after the barrier of pass
-  // p - 2, next set in pass p + 1), so one barrier per pass suffices
-  __shared__ uint32_t flag[3];
-  if (threadIdx.x < 3) flag[threadIdx.x] = 0;
+  // points that rose in pass p: E.rose[p % 3], added to by the waves, read by
+  // all after the pass's barrier; thread 0 clears slot (p + 1) % 3 during pass
+  // p (last read after the barrier of pass p - 2, next added to in pass
+  // p + 1), so one barrier per pass suffices
+  if (threadIdx.x < 3) E.rose[threadIdx.x] = 0;
+  if (threadIdx.x == 0) {
+    dense = 0;
+    E.over = 0;
+  }
   __syncthreads();
+  if (!listed && lane() == 0) dense = 1;
   constexpr int NW = (NJ + 3) / 4;
-  uint32_t pk[PK && TZ > 1 ? G::PER : 1][NW];
-  if constexpr (PK && TZ > 1) {
+  uint32_t pk[PK ? G::PER : 1][NW];
+  if constexpr (PK) {
 #pragma unroll
     for (int k = 0; k < G::PER; ++k) spread_mask<NW>(mk[k], pk[k]);
   }
-  int iters = 0;
+  int iters = 0, total = 0;
+  bool events = false;
+  uint32_t nev = 0;  // the wave's first events
   for (;;) {
-    int changed = 0;
-    if (threadIdx.x == 0) flag[(iters + 1) % 3] = 0;
+    uint32_t changed = 0;  // bit k: slot k rose (a listed wave: bit 0)
+    if (threadIdx.x == 0) E.rose[(iters + 1) % 3] = 0;
     if (listed) {
       if (my_pt && step((int)(my_pt & 4095u), my_pt >> 12, my_cd)) changed = 1;
     } else {
       // Gauss-Seidel along the thread's slots (one column of points along
-      // z in a 3D tile, one row in four in a 2D tile), in alternating
-      // directions from pass to pass, so a chain along that axis crosses
-      // the tile in a pass or two whichever way it runs
-      if constexpr (PK && TZ > 1) {
-        // the slots' masks spread over bytes once per run (below), slot
-        // order fixed at compile time in both directions
-        auto visit = [&](int k) {
-          if (!mk[k]) return;
-          const int li = li0 + k * G::kSlot;
-          const uint32_t cur = S[li];
-          const uint32_t best = dense_best_pk<NJ, G::HX, G::HY * G::HX>(S, li, pk[k], cur);
-          if (best > cur) {
-            S[li] = best;
-            changed = 1;
-          }
-        };
+      // z), in alternating directions from pass to pass, so a chain along
+      // that axis crosses the tile in a pass or two whichever way it runs
+      auto visit = [&](int k) {
+        const uint32_t m = mk[k];
+        if (!m) return;
+        const int li = li0 + k * G::kSlot;
+        const uint32_t w = P[li], cur = w & 0xffffu;
+        uint32_t best;
+        if constexpr (PK) best = pull_best_pk<NJ, G::HX, G::HY * G::HX>(P, li, m, pk[k], cur);
+        else best = pull_best<NJ, G::HX, G::HY * G::HX>(P, li, m, cur);
+        if (best > cur) {
+          P[li] = w + (best - cur);
+          changed |= 1u << k;
+        }
+      };
+      if constexpr (PK) {
+        // slot order fixed at compile time in both directions
         if (iters & 1) {
 #pragma unroll
           for (int kk = 0; kk < G::PER; ++kk) visit(G::PER - 1 - kk);
@@ -547,21 +756,70 @@ __device__ void relax(uint32_t* S, const uint16_t* mk, uint32_t* counters,
           for (int kk = 0; kk < G::PER; ++kk) visit(kk);
         }
       } else {
-      const bool rev = iters & 1;
+        const bool rev = iters & 1;
 #pragma unroll 2
-      for (int kk = 0; kk < G::PER; ++kk) {
-        const int k = rev ? G::PER - 1 - kk : kk;
-        const uint32_t m = mk[k];
-        if (!m) continue;
-        const int li = li0 + k * G::kSlot;
-        const uint32_t cur = S[li];
-        // every stencil neighbour at once (one LDS round trip), masked
-        const uint32_t best = dense_best<NJ, G::HX, G::HY * G::HX>(S, li, m, cur);
-        if (best > cur) {
-          S[li] = best;
-          changed = 1;
-        }
+        for (int kk = 0; kk < G::PER; ++kk) visit(rev ? G::PER - 1 - kk : kk);
       }
+    }
+    count_rose<G::PER>(E, changed, iters % 3);
+    __syncthreads();
+    const uint32_t c = E.rose[iters % 3];
+    ++total;
+    if (!c) break;
+    if (++iters > G::NPT + 2) {  // unreachable: the order inside a tile is acyclic
+      if (threadIdx.x == 0) atomicOr(&counters[0], 1u);
+      break;
+    }
+    if (c <= kEventShare<G::NPT> && dense) {
+      uint16_t* l0 = E.list[w][0];
+      if (listed) {
+        list_points(l0, nev, changed != 0u, (int)(my_pt & 4095u));
+      } else {
+#pragma unroll
+        for (int k = 0; k < G::PER; ++k)
+          list_points(l0, nev, (changed >> k) & 1u, li0 + k * G::kSlot);
+      }
+      events = true;
+      break;
+    }
+  }
+  if (events) {
+    total += push_rounds<TZ, TY, TX>(P, E, nev);
+    __syncthreads();
+    if (E.over) total += word_passes<TZ, TY, TX>(P, E, counters);
+  }
+  if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)total);
+}
+
+// Local fixed point of a tile whose subbins may not fit the 16 bits of an LDS
+// word: passes over the owned points (S: subbins, 32 bits; mk: flags), slots
+// in alternating order, until none rises.
+template <int TZ, int TY, int TX>
+__device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
+                           unsigned long long* itot, uint32_t t) {
+  using G = TileGeom<TZ, TY, TX>;
+  constexpr int NJ = TZ == 1 ? 6 : 14;
+  const int li0 = G::local(threadIdx.x);
+  // flag[p % 3]: some point rose in pass p (rotating as E.rose in relax)
+  __shared__ uint32_t flag[3];
+  if (threadIdx.x < 3) flag[threadIdx.x] = 0;
+  __syncthreads();
+  int iters = 0;
+  for (;;) {
+    bool changed = false;
+    if (threadIdx.x == 0) flag[(iters + 1) % 3] = 0;
+    const bool rev = iters & 1;
+#pragma unroll 1
+    for (int kk = 0; kk < G::PER; ++kk) {
+      const int k = rev ? G::PER - 1 - kk : kk;
+      const uint32_t m = mk[k];
+      if (!m) continue;
+      const int li = li0 + k * G::kSlot;
+      const uint32_t cur = S[li];
+      const uint32_t best = dense_best<NJ, G::HX, G::HY * G::HX>(S, li, m, cur);
+      if (best > cur) {
+        S[li] = best;
+        changed = true;
       }
     }
     if (__ballot(changed) && lane() == 0) flag[iters % 3] = 1;
@@ -575,226 +833,108 @@ __device__ void relax(uint32_t* S, const uint16_t* mk, uint32_t* counters,
   if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)(iters + 1));
 }
 
-// ------------------------------------------------------------------ levels
-// 2D tiles.  The level of an owned point is the length of the longest path
-// of same-bin lower neighbours inside the tile that ends at it (0: no lower
-// neighbour inside).  Taking the points level by level, each after every
-// level below it, visits every point once with all its lower neighbours
-// already final: one pass in a topological order of the tile's part of the
-// order graph reaches the tile's fixed point for a fixed halo (the raising
-// rule of Alg. 2).  The first pass finds the levels by peeling (Kahn's
-// order: a point is ready once all its lower neighbours inside the tile are
-// done) and keeps them, one byte per point, saturating at 255; later runs
-// of the tile sort their points by the kept levels.  A 2D tile holds eight
-// slots per thread, so a relaxation pass costs eight visits per wave, while
-// a level costs one visit of the waves its points fall to: levels pay off
-// there.  3D tiles (four slots per thread, and more levels per tile) keep
-// the relaxation passes.
-
-// stencil offsets j of owned point i whose neighbour lies inside the tile
+// ------------------------------------------------------------------ peeling
+// First pass of a 2D tile.  2D fields are smooth on the scale of a tile and
+// most of their points have same-bin neighbours, so relaxation passes would
+// visit every point many times.  The points are taken in a topological order
+// of the tile's part of the order graph instead (Kahn's order): a point is
+// ready once all its lower neighbours inside the tile are done, and then takes
+// its final value at once (the raising rule of Alg. 2 for a fixed halo).
+// The LDS word of an owned point counts its unfinished lower neighbours inside
+// the tile in bits 22..24.  A ready point reads its six neighbours' words at
+// once (one LDS round trip): its own raise from those its flags name, and the
+// dependents, whose flags name it, are counted down by LDS atomics issued
+// together; those that reach zero are listed for the next level.  The list
+// holds every point once.  Levels of at most 64 points, and those after them,
+// run on wave 0 alone without block barriers.  Returns the levels of this
+// wave; ends with a block barrier.
+constexpr int kLeftShift = 22;
 template <int TZ, int TY, int TX>
-__device__ __forceinline__ uint32_t inside_bits(int i) {
-  constexpr int NJ = TZ == 1 ? 6 : 14;
-  const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-  uint32_t b = 0;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int z = iz + kOff[j][0], y = iy + kOff[j][1], x = ix + kOff[j][2];
-    if (z >= 0 && z < TZ && y >= 0 && y < TY && x >= 0 && x < TX) b |= 1u << j;
-  }
-  return b;
-}
-
-// owned-index offset of stencil offset j (known only at run time)
-template <int TZ, int TY, int TX>
-__device__ __forceinline__ int own_off(int j) {
-  return off_z(j) * (TY * TX) + off_y(j) * TX + off_x(j);
-}
-
-// the best raise of the point at LDS index li (lower-neighbour mask m)
-template <int TZ, int TY, int TX>
-__device__ __forceinline__ uint32_t raise_of(const uint32_t* S, int li, uint32_t m, uint32_t cur) {
+__device__ __forceinline__ int peel(uint32_t* P, uint16_t* list, uint32_t* tail) {
   using G = TileGeom<TZ, TY, TX>;
-  constexpr int NJ = TZ == 1 ? 6 : 14;
-  if (__ballot(__popc(m) > 3)) return dense_best<NJ, G::HX, G::HY * G::HX>(S, li, m, cur);
-  uint32_t best = cur;
-  while (m) {
-    const int j = __builtin_ctz(m);
-    m &= m - 1;
-    const uint32_t c = S[li + off_lin(j, G::HX, G::HY * G::HX)] + ((j & 1) ? 0u : 1u);
-    best = c > best ? c : best;
-  }
-  return best;
-}
-
-// LDS of the peeling pass: per owned point its masks (lower | inside upper
-// << 16), its count of unfinished lower neighbours inside the tile (bytes),
-// its level (bytes) and the ready list; three list counters.
-template <int TZ, int TY, int TX>
-struct KahnLds {
-  static constexpr int NPT = TZ * TY * TX;
-  static constexpr int kBytes = NPT * 4 + NPT + NPT + NPT * 2 + 16;
-};
-
-// First pass of a tile with the halo subbins at 0: peel the tile's points
-// level by level (a point joins the ready list when its last lower
-// neighbour inside the tile is done) and raise each as it is taken.  Leaves
-// the levels in lvb.  Every thread must call it; returns the number of
-// levels (block-uniform).
-template <int TZ, int TY, int TX>
-__device__ int kahn_relax(uint32_t* S, uint8_t* lds, const uint16_t* mk, const uint16_t* up,
-                          uint8_t*& lvb_out) {
-  using G = TileGeom<TZ, TY, TX>;
-  constexpr int NPT = G::NPT;
-  uint32_t* W = (uint32_t*)lds;
-  uint32_t* cnt4 = (uint32_t*)(lds + NPT * 4);
-  uint8_t* cnt = (uint8_t*)cnt4;
-  uint8_t* lvb = lds + NPT * 4 + NPT;
-  uint16_t* list = (uint16_t*)(lds + NPT * 6);
-  uint32_t* kc = (uint32_t*)(lds + NPT * 8);
-  lvb_out = lvb;
-  if (threadIdx.x < 3) kc[threadIdx.x] = 0;
-  uint32_t deg[G::PER], wk[G::PER];
+  static_assert(TZ == 1, "2D tiles");
+  constexpr int NJ = 6, HX = G::HX, HXY = G::HY * G::HX;
+  const int li0 = G::local(threadIdx.x);
+  if (threadIdx.x == 0) *tail = 0;
+  __syncthreads();  // the words, too
+  // level 0: nothing below inside the tile
 #pragma unroll
   for (int k = 0; k < G::PER; ++k) {
-    const int i = threadIdx.x + k * kThreads;
-    const uint32_t inb = inside_bits<TZ, TY, TX>(i);
-    wk[k] = (uint32_t)mk[k] | (uint32_t)(up[k] & inb) << 16;
-    deg[k] = (uint32_t)__popc(mk[k] & inb);
-    W[i] = wk[k];
-    cnt[i] = (uint8_t)deg[k];
-    lvb[i] = 0;
+    const int li = li0 + k * G::kSlot;
+    const bool go = (P[li] >> kLeftShift & 7u) == 0;
+    const uint64_t b = __ballot(go);
+    if (!b) continue;
+    uint32_t base = 0;
+    if (lane() == 0) base = atomicAdd(tail, (uint32_t)__popcll(b));
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    if (go) list[base + lane_prefix(b)] = (uint16_t)li;
   }
   __syncthreads();
-  // level 0: nothing below inside the tile, and something to do (a lower
-  // neighbour in the halo to raise from, or upper neighbours to release)
-#pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    const bool go = deg[k] == 0 && wk[k] != 0;
-    const uint64_t rb = __ballot(go);
-    if (rb) {
-      uint32_t base = 0;
-      if (lane() == 0) base = atomicAdd(&kc[0], (uint32_t)__popcll(rb));
-      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-      if (go) list[base + lane_prefix(rb)] = (uint16_t)(threadIdx.x + k * kThreads);
-    }
-  }
-  __syncthreads();
-  int beg = 0, end = (int)kc[0], level = 0;
+  uint32_t beg = 0, end = (uint32_t)__builtin_amdgcn_readfirstlane((int)*tail);
+  bool narrow = false;
+  int level = 0;
   while (beg < end) {
-    const int nxt = (level + 1) % 3;
-    if (threadIdx.x == 0) kc[(level + 2) % 3] = 0;  // read two levels ago, appended next level
-    for (int e = beg + (int)threadIdx.x; e < end; e += kThreads) {
-      const int i = list[e];
-      const uint32_t w = W[i];
-      const uint32_t m = w & 0xffffu;
-      if (m) {
-        const int li = G::local(i);
-        const uint32_t cur = S[li];
-        const uint32_t b = raise_of<TZ, TY, TX>(S, li, m, cur);
-        if (b > cur) S[li] = b;
+    narrow = narrow || end - beg <= 64;
+    if (narrow && wave() != 0) break;
+    if (!narrow) __syncthreads();  // every wave has read *tail
+    uint32_t made = 0;             // narrow: points listed by this level
+    for (uint32_t b = beg + (narrow ? 0u : (uint32_t)wave() * 64); b < end;
+         b += narrow ? 64u : (uint32_t)kThreads) {
+      const bool act = b + (uint32_t)lane() < end;
+      const int p = act ? (int)list[b + lane()] : li0;
+      const uint32_t wp = P[p];
+      uint32_t q[NJ], c[NJ], old[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) q[j] = P[p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]];
+      const uint32_t m = (~wp >> 16) & 0x3fu;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        c[j] = and_word(q[j], (uint32_t)((int32_t)(m << (31 - j)) >> 31));
+      const uint32_t best = fold_cands<NJ>(c, m, wp & 0xffffu);
+      if (act) P[p] = (wp & 0xffff0000u) | best;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        // neighbour j names p in its flag j ^ 1 (clear) and lies in the tile
+        old[j] = 0;
+        if (act && !(q[j] & (kHalo | 1u << (16 + (j ^ 1)))))
+          old[j] = atomicSub(&P[p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]],
+                             1u << kLeftShift);
       }
-      lvb[i] = (uint8_t)(level < 255 ? level : 255);
-      uint32_t u = w >> 16;
-      while (u) {
-        const int j = __builtin_ctz(u);
-        u &= u - 1;
-        const int q = i + own_off<TZ, TY, TX>(j);
-        const uint32_t sh = 8u * (uint32_t)(q & 3);
-        const uint32_t old = atomicSub(&cnt4[q >> 2], 1u << sh);
-        const bool ready = ((old >> sh) & 0xffu) == 1u;
-        const uint64_t rb = __ballot(ready);
-        if (rb) {
-          const int leader = __builtin_ctzll(rb);
-          uint32_t base = 0;
-          if (lane() == leader) base = atomicAdd(&kc[nxt], (uint32_t)__popcll(rb));
-          base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
-          if (ready) list[end + base + lane_prefix(rb)] = (uint16_t)q;
-        }
+      uint64_t rb[NJ];
+      uint32_t tot = 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        rb[j] = __ballot((old[j] >> kLeftShift & 7u) == 1u);
+        tot += (uint32_t)__popcll(rb[j]);
+      }
+      if (!tot) continue;
+      uint32_t pos = end + made;
+      if (narrow) {
+        made += tot;
+      } else {
+        if (lane() == 0) pos = atomicAdd(tail, tot);
+        pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if ((rb[j] >> lane()) & 1u)
+          list[pos + lane_prefix(rb[j])] =
+              (uint16_t)(p + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]);
+        pos += (uint32_t)__popcll(rb[j]);
       }
     }
-    __syncthreads();
     beg = end;
-    end += (int)kc[nxt];
+    if (narrow) {
+      end += made;
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      __syncthreads();
+      end = (uint32_t)__builtin_amdgcn_readfirstlane((int)*tail);
+    }
     ++level;
   }
+  __syncthreads();
   return level;
-}
-
-// A later run of a tile: its points sorted by their kept levels (lv, 255 =
-// unknown), then raised level by level.  Levels of at most 64 points run on
-// wave 0 alone, with no block barrier between consecutive ones (a wave's
-// LDS accesses are ordered); a block barrier separates the rest.  Returns
-// the number of levels, or -1 (block-uniform) when some point's level is
-// unknown, before touching S.
-template <int TZ, int TY, int TX>
-__device__ int level_relax(uint32_t* S, const uint16_t* mk, const uint8_t* lv) {
-  using G = TileGeom<TZ, TY, TX>;
-  __shared__ uint32_t hist[257];
-  __shared__ uint32_t list[G::NPT];
-  for (int h = threadIdx.x; h < 257; h += kThreads) hist[h] = 0;
-  __syncthreads();
-  bool unknown = false;
-#pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    if (mk[k]) {
-      if (lv[k] == 255) unknown = true;
-      else atomicAdd(&hist[lv[k]], 1u);
-    }
-  }
-  if (__syncthreads_or(unknown)) return -1;
-  if (threadIdx.x < 64) {
-    // exclusive scan of the 255 counts, four per lane; hist[256] = levels
-    uint32_t v[4], t = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      v[q] = hist[4 * lane() + q];
-      t += v[q];
-    }
-    const uint32_t incl = wave_scan_u32(t);
-    uint32_t run = incl - t;
-    int top = -1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      hist[4 * lane() + q] = run;
-      run += v[q];
-      if (v[q]) top = 4 * lane() + q;
-    }
-    top = wave_reduce(top, OpMax{});
-    if (lane() == 0) hist[256] = (uint32_t)(top + 1);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    if (mk[k]) {
-      const uint32_t pos = atomicAdd(&hist[lv[k]], 1u);
-      list[pos] = (uint32_t)(threadIdx.x + k * kThreads) | (uint32_t)mk[k] << 12;
-    }
-  }
-  __syncthreads();
-  // hist[l] is now the end of level l
-  const int nlev = (int)hist[256];
-  int beg = 0;
-  bool wide = false;
-  for (int l = 0; l < nlev; ++l) {
-    const int end = (int)hist[l];
-    const bool w = end - beg > 64;
-    if (w || wide) {
-      __syncthreads();
-      wide = false;
-    }
-    for (int e = beg + (int)threadIdx.x; e < end; e += kThreads) {
-      const uint32_t ent = list[e];
-      const int li = G::local((int)(ent & 4095u));
-      const uint32_t cur = S[li];
-      const uint32_t b = raise_of<TZ, TY, TX>(S, li, ent >> 12, cur);
-      if (b > cur) S[li] = b;
-    }
-    wide = wide || w;
-    beg = end;
-  }
-  __syncthreads();
-  return nlev;
 }
 
 // mark the neighbour tiles in `dirs` (27-bit set, see out_dirs) for sweep
@@ -1024,292 +1164,324 @@ __device__ void q_finish(uint32_t dirs, uint32_t t, const TileCoord& c, const Ti
     __hip_atomic_fetch_add(&Q.q->pending, -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Same-bin flags of an owned point of a float64 tile whose halo bins span
-// 2^31 or more: every neighbour in the grid re-quantized from its key (one
-// at a time; a rare path).
-template <int K, int TZ, int TY, int TX>
-__device__ __forceinline__ uint32_t wide_same(const int64_t* Pk, int li, int64_t b, double inv,
-                                              int z, int y, int x, const Box& box) {
+template <int TZ, int TY, int TX>
+__constant__ const Faces<TZ, TY, TX> kFaces{};
+
+// A lane's point on face slot f of the tile at c: its LDS index (-1: none),
+// offset from the field's first point (g00: the tile's first point) and
+// whether it lies in the grid.
+struct FacePoint {
+  int li;
+  int64_t g;
+  bool in;
+};
+__device__ __forceinline__ FacePoint face_point(const FaceSlot& f, const TileCoord& c,
+                                                const Box& box, int64_t g00) {
+  // (a plane has fewer than 2^32 points, so steps are 32-bit factors)
+  const uint32_t nx = (uint32_t)box.nx, nyx = (uint32_t)box.ny * (uint32_t)box.nx;
+  const uint32_t r = (uint32_t)f.r0 + (uint32_t)lane();
+  const uint32_t u = __umul24(r, (uint32_t)f.magic) >> 16, v = r - __umul24(u, (uint32_t)f.width);
+  const bool uz = f.ua == 2, vy = f.va == 1;
+  const uint32_t lz = (uint32_t)box.nz, ly = (uint32_t)box.ny;
+  const uint32_t bz = (uint32_t)(c.z0 + f.z), by = (uint32_t)(c.y0 + f.y),
+                 bx = (uint32_t)(c.x0 + f.x);
+  const uint32_t gu = uz ? nyx : nx, gv = vy ? nx : 1u;
+  const uint32_t lu = uz ? lz : ly, lv = vy ? ly : nx, bu = uz ? bz : by, bv = vy ? by : bx;
+  // the axis the face is normal to (neither u's nor v's): in the grid for all
+  // of it or none
+  const uint32_t pn = vy ? bx : uz ? by : bz, ln = vy ? nx : uz ? ly : lz;
+  // lanes of the slot past the face, or none where the face is outside
+  const uint32_t lim = pn < ln ? (uint32_t)f.cnt : 0u;
+  FacePoint p;
+  p.in = (r < lim) & (bu + u < lu) & (bv + v < lv);
+  const int64_t g0 = g00 + (int64_t)f.z * (int64_t)nyx + (int64_t)f.y * (int64_t)nx + f.x;
+  p.g = (int64_t)((uint64_t)g0 + (uint64_t)v * gv + (uint64_t)u * gu);
+  p.li = r < (uint32_t)f.cnt ? f.li + (int)__umul24(u, (uint32_t)f.lu) + (int)__umul24(v, (uint32_t)f.lv)
+                             : -1;
+  return p;
+}
+// The neighbour tile of halo cell li as its bit of the 27-direction set.
+template <int TZ, int TY, int TX>
+__device__ __forceinline__ uint32_t cell_dir(int li) {
   using G = TileGeom<TZ, TY, TX>;
-  constexpr int NJ = TZ == 1 ? 6 : 14;
-  uint32_t sm = 0;
-#pragma unroll 1
-  for (int j = 0; j < NJ; ++j) {
-    const int zz = z + off_z(j), yy = y + off_y(j), xx = x + off_x(j);
-    if (zz < 0 || zz >= box.nz || yy < 0 || yy >= box.ny || xx < 0 || xx >= box.nx) continue;
-    const int64_t kq = Pk[li + off_lin(j, G::HX, G::HY * G::HX)];
-    sm |= (uint32_t)(Traits<8>::q(Traits<8>::to_double(Traits<8>::unkey(kq)), inv) == b) << j;
-  }
-  return sm;
+  const int hz = li / (G::HY * G::HX), hy = (li / G::HX) % G::HY, hx = li % G::HX;
+  const int dz = G::ZO ? (hz == 0 ? 0 : hz == G::HZ - 1 ? 2 : 1) : 1,
+            dy = hy == 0 ? 0 : hy == G::HY - 1 ? 2 : 1, dx = hx == 0 ? 0 : hx == G::HX - 1 ? 2 : 1;
+  return 1u << (dz * 9 + dy * 3 + dx);
 }
 
-// First pass, fused: build the order flags of the owned points (a2, the
-// flags of Alg. 1) from the bins and values of the tile and its halo, write
-// them, then relax with halo subbins 0 (the first sweep of a3).
-// Returns (block-uniform) the neighbour tiles to sweep next: those holding a
-// point that has a nonzero boundary point of this tile as a same-bin lower
-// neighbour (only their relaxation depends on it).
+// m becomes 2m + (a and b of the lane): the conditions as lane masks, joined on
+// the scalar side, shifted in by one add with carry.
+__device__ __forceinline__ uint32_t shift_in(uint32_t m, uint64_t a, uint64_t b) {
+  uint32_t r;
+  asm("s_and_b64 vcc, %2, %3\n\tv_addc_co_u32_e32 %0, vcc, %1, %1, vcc"
+      : "=v"(r) : "v"(m), "s"(a), "s"(b) : "vcc", "scc");
+  return r;
+}
+
+// Bin of value y in the first pass (Sec. IV-A): q_bin / q_bin32 with the
+// common case branch-free.  float32: the conversion saturates, so a product
+// out of range gives a bin outside the limits.  float64: below 2^51 the
+// rounded product plus 1.5 * 2^52 holds the integer in its low bits.
+template <int K>
+__device__ __forceinline__ int64_t first_bin(double y, double inv, bool& bad) {
+  const double p = y * inv;
+  double q = rint(p);
+  if (fabs(p - q) == 0.5) {
+    const double r = fma(y, inv, -p);
+    if (r != 0.0) q = r > 0.0 ? p + 0.5 : p - 0.5;
+  }
+  if constexpr (K == 4) {
+    int32_t b;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(b) : "v"(q));
+    bad |= (uint32_t)b + 0x7ffffffeu > 0xfffffffcu;  // |b| > 2^31 - 2
+    return b;
+  } else {
+    int64_t b = __double_as_longlong(q + 6755399441055744.0) - 0x4338000000000000ll;
+    if (!(fabs(p) < 2251799813685248.0)) {
+      b = q_bin(y, inv);
+      bad |= b > Traits<8>::kBinLimit || b < -Traits<8>::kBinLimit;
+    }
+    return b;
+  }
+}
+
+// First pass of a tile, fused: quantize (a1), the order flags of the owned
+// points (a2, the flags of Alg. 1), and the first relaxation (the first sweep
+// of a3) with halo subbins 0 or, for hc >= 0, those of the neighbour tiles of
+// colour hc.  Returns (block-uniform) the neighbour tiles to sweep next.
+// The values of the owned points and of the face points around them come in
+// once, all loads in flight together; each is quantized once (Sec. IV-A).  In LDS a point holds its value
+// and its bin (float64: the low 32 bits of the bin's distance from the tile's
+// first bin, which decide equality whenever no bin is 2^30 or more from it,
+// else the tile is wide and re-quantizes); a point outside the grid holds a
+// bin that no point has, so no comparison needs a bounds check.  An order flag
+// is two comparisons, their conjunction on the scalar side and one add with
+// carry.  The neighbour tiles to sweep next are found at the end from the
+// face points: those with a same-bin lower neighbour in the tile that rose and
+// would raise them.
+constexpr int32_t kNoBin = (int32_t)0x80000000;
+template <int NPT>
+struct ReadyLds {
+  uint16_t list[NPT];
+  uint32_t tail;
+};
 template <int K, int TZ, int TY, int TX>
-__device__ __forceinline__ uint32_t tile0_body(const typename Traits<K>::Raw* __restrict__ x, Box box,
-                           Tiling tl, Params* prm, typename Traits<K>::Bin* __restrict__ bins,
-                           uint16_t* __restrict__ mask, uint32_t* __restrict__ sub,
-                           uint32_t* counters, unsigned long long* itot, uint32_t t,
-                           TileCoord& c, int hc = -1) {
-  using Tr = Traits<K>;
+struct FirstLds {
   using G = TileGeom<TZ, TY, TX>;
-  using Key = typename Tr::Bin;  // keys fit the signed type of the bins
-  using Bin = typename Tr::Bin;
-  // float32: key and bin of a halo point side by side, one 8-byte LDS read
-  // per neighbour.  float64: the 8-byte key, and the low 32 bits of the bin
-  // (12 instead of 16 bytes per point), which decide equality of two bins
-  // exactly whenever the halo's bins span less than 2^31; a tile whose bins
-  // span more ("wide") re-quantizes a neighbour's value to compare bins.
-  using KB = uint2;
-  constexpr int NJ = TZ == 1 ? 6 : 14;  // 2D: only the in-plane offsets
-  constexpr int kKB = G::H * (K == 4 ? 8 : 12);
-  // the subbins of the halo, then (2D) the peeling state, reuse the buffer
-  constexpr int kS = G::H * 4 + (TZ == 1 ? KahnLds<TZ, TY, TX>::kBytes : 0);
-  constexpr int kBytes = kKB > kS ? kKB : kS;
-  constexpr int HL = (G::H + kThreads - 1) / kThreads;  // halo loads per thread
-  __shared__ __attribute__((aligned(16))) uint8_t buf[kBytes];
-  KB* P = (KB*)buf;                                  // float32
-  int64_t* Pk = (int64_t*)buf;                       // float64: keys
-  int32_t* Pb = (int32_t*)(buf + (K == 8 ? G::H * 8 : 0));  // float64: bin offsets
-  uint32_t* S = (uint32_t*)buf;  // reused once the flags are built
-  __shared__ int64_t s_rng[2][kWaves];  // float64: per-wave least / greatest bin
-  int64_t bref = 0;   // float64: the halo's lowest bin
-  bool wide = false;  // float64: the halo's bins span 2^31 or more
-
+  typename Traits<K>::Raw x[G::H];  // values
+  int32_t b[G::H];                  // bins
+  uint32_t P[G::H];                 // LDS words of the relaxation
+  // 3D: relaxation; 2D: peeling
+  std::conditional_t<(TZ > 1), EventLds<G::NPT>, ReadyLds<G::NPT>> E;
+  uint32_t wide, dirs;
+};
+template <int K, int TZ, int TY, int TX>
+__device__ __forceinline__ uint32_t tile0_body(
+    const typename Traits<K>::Raw* __restrict__ x, Box box, Tiling tl, Params* prm,
+    typename Traits<K>::Bin* __restrict__ bins, uint16_t* __restrict__ mask,
+    uint32_t* __restrict__ sub, uint32_t* counters, unsigned long long* itot, uint32_t t,
+    TileCoord& c, int hc = -1) {
+  using Tr = Traits<K>;
+  using Raw = typename Tr::Raw;
+  using Val = std::conditional_t<K == 4, float, double>;
+  using G = TileGeom<TZ, TY, TX>;
+  using F = Faces<TZ, TY, TX>;
+  constexpr int HXY = G::HY * G::HX, NJ = TZ == 1 ? 6 : 14;
+  __shared__ __attribute__((aligned(16))) FirstLds<K, TZ, TY, TX> lds;
+  const Val* X = (const Val*)lds.x;
+  int32_t* B = lds.b;
+  uint32_t* P = lds.P;
+  auto val = [](Raw u) -> Val {
+    if constexpr (K == 4) return __uint_as_float(u);
+    else return __longlong_as_double((long long)u);
+  };
   c = tile_coord<TZ, TY, TX>(t, tl);
-  {
-    // the values of the halo (every load issued first); their bins are
-    // computed here (Sec. IV-A), not read back from a separate pass
-    typename Tr::Raw u[HL];
-    // a halo inside the grid (most tiles): 32-bit offsets from the halo's
-    // first point, every load unconditional, no bounds checks
-    const bool hin = c.z0 - G::ZO >= 0 && c.z0 + TZ - 1 + G::ZO < box.nz && c.y0 >= 1 &&
-                     c.y0 + TY < box.ny && c.x0 >= 1 && c.x0 + TX < box.nx &&
-                     (uint64_t)box.ny * (uint64_t)box.nx * G::HZ < (1ull << 31);
-    if (hin) {
-      const int64_t g0 = ((int64_t)(c.z0 - G::ZO) * box.ny + (c.y0 - 1)) * box.nx + (c.x0 - 1);
-      const uint32_t nyx = (uint32_t)box.ny * (uint32_t)box.nx;
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        const uint32_t hz = (uint32_t)i / (G::HY * G::HX), hy = ((uint32_t)i / G::HX) % G::HY,
-                       hx = (uint32_t)i % G::HX;
-        const bool in = i < G::H;
-        const typename Tr::Raw v =
-            x[in ? g0 + (int64_t)(hz * nyx + hy * (uint32_t)box.nx + hx) : 0];
-        u[q] = in ? v : (typename Tr::Raw)0;
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        u[q] = 0;
-        if (i < G::H) {
-          int hz = i / (G::HY * G::HX), hy = (i / G::HX) % G::HY, hx = i % G::HX;
-          int z = c.z0 + hz - G::ZO, y = c.y0 + hy - 1, xx = c.x0 + hx - 1;
-          if (z >= 0 && z < box.nz && y >= 0 && y < box.ny && xx >= 0 && xx < box.nx)
-            u[q] = x[((int64_t)z * box.ny + y) * box.nx + xx];
-        }
-      }
-    }
-    const double inv = prm->inv;
-    bool bad_v = false, bad_r = false;
-    if constexpr (K == 4) {
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        if (i < G::H) {
-          bad_v |= !Tr::finite(u[q]);
-          const int64_t bq = Tr::q(Tr::to_double(u[q]), inv);
-          bad_r |= bq > Tr::kBinLimit || bq < -Tr::kBinLimit;
-          KB e;
-          e.x = (uint32_t)(Key)Tr::key(u[q]);
-          e.y = (uint32_t)(Bin)bq;
-          P[i] = e;
-        }
-      }
-    } else {
-      // bins of the halo points in the grid (others are never compared),
-      // their least and greatest over the block, then keys and offsets
-      int64_t lo = INT64_MAX, hi = INT64_MIN;
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        if (i < G::H) {
-          bad_v |= !Tr::finite(u[q]);
-          const int64_t bq = Tr::q(Tr::to_double(u[q]), inv);
-          bad_r |= bq > Tr::kBinLimit || bq < -Tr::kBinLimit;
-          Pk[i] = Tr::key(u[q]);
-          Pb[i] = (int32_t)(uint32_t)(uint64_t)bq;
-          const int hz = i / (G::HY * G::HX), hy = (i / G::HX) % G::HY, hx = i % G::HX;
-          const int z = c.z0 + hz - G::ZO, y = c.y0 + hy - 1, xx = c.x0 + hx - 1;
-          if (z >= 0 && z < box.nz && y >= 0 && y < box.ny && xx >= 0 && xx < box.nx) {
-            lo = bq < lo ? bq : lo;
-            hi = bq > hi ? bq : hi;
-          }
-        }
-      }
-      lo = wave_reduce(lo, OpMin{});
-      hi = wave_reduce(hi, OpMax{});
-      if (lane() == 0) {
-        s_rng[0][wave()] = lo;
-        s_rng[1][wave()] = hi;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        lo = s_rng[0][w] < lo ? s_rng[0][w] : lo;
-        hi = s_rng[1][w] > hi ? s_rng[1][w] : hi;
-      }
-      // hi >= lo: the tile's owned points lie in the grid
-      bref = lo;
-      wide = (uint64_t)hi - (uint64_t)lo >= (1ull << 31);
-    }
-    if (bad_v) set_status(prm, ST_NONFINITE);
-    if (bad_r) set_status(prm, ST_RANGE);
-  }
-  __syncthreads();
-  // key and bin of the halo point at LDS index l (the bin compared with
-  // another point's only for equality, so float64 uses its offset)
-  auto key_at = [&](int l) -> Key {
-    if constexpr (K == 4) return (Key)(int32_t)P[l].x;
-    else return (Key)Pk[l];
+  const int w = __builtin_amdgcn_readfirstlane(wave());
+  const int li0 = G::local(threadIdx.x);
+  const int64_t nyx = (int64_t)box.ny * box.nx;
+  const int64_t g00 = ((int64_t)c.z0 * box.ny + c.y0) * box.nx + c.x0;
+  // slot k of a thread: k planes (2D: k times kRows rows) after slot 0
+  constexpr int PZ = G::PER, kRows = kThreads / TX;
+  const int iy = (int)threadIdx.x / TX, ix = (int)threadIdx.x % TX;
+  const int64_t g0 = g00 + (int64_t)iy * box.nx + ix;
+  const int64_t gstep = TZ > 1 ? nyx : (int64_t)kRows * box.nx;
+  const bool in0 = (TZ == 1 || c.y0 + iy < box.ny) && c.x0 + ix < box.nx;
+  auto in = [&](int k) {
+    return in0 && (TZ > 1 ? c.z0 + k < box.nz : c.y0 + iy + k * kRows < box.ny);
   };
-  auto bin_at = [&](int l) -> int64_t {
-    if constexpr (K == 4) return (int64_t)(int32_t)P[l].y;
-    else return (int64_t)Pb[l];  // low 32 bits: equality only (not wide)
+  // values: the owned points, the face points (points outside the grid read
+  // the tile's first)
+  Raw u[PZ], hu[F::kPer];
+  int hl[F::kPer];
+  uint32_t hin = 0;  // bit q: face point q lies in the grid
+#pragma unroll
+  for (int k = 0; k < PZ; ++k) u[k] = x[in(k) ? g0 + k * gstep : g00];
+  uint32_t hs[F::kPer];  // subbins of the face points of colour hc
+#pragma unroll
+  for (int q = 0; q < F::kPer; ++q) {
+    hl[q] = -1;
+    hu[q] = 0;
+    hs[q] = 0;
+    if (w + q * kWaves >= F::kSlots) continue;
+    const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], c, box, g00);
+    hu[q] = x[f.in ? f.g : g00];
+    hin |= (uint32_t)f.in << q;
+    hl[q] = f.li;
+    if (hc >= 0) {
+      // tiles across one face or one corner have the other colour, across an
+      // edge the same; those of colour hc are final from an earlier launch
+      const uint32_t d = cell_dir<TZ, TY, TX>(f.li < 0 ? 0 : f.li);
+      const bool take = f.in && !(d & same_colour_dirs());
+      const uint32_t v = sub[take ? f.g : g00];
+      hs[q] = take ? v : 0u;
+    }
+  }
+  if (threadIdx.x == 0) {
+    lds.wide = 0;
+    lds.dirs = 0;
+  }
+  const double inv = prm->inv;
+  bool bad_v = false, bad_r = false, far = false;
+  const int64_t bref =
+      K == 8 ? first_bin<K>(Tr::to_double(x[g00]), inv, bad_r) : 0;
+  auto low = [&](int64_t b) -> int32_t {
+    if constexpr (K == 4) return (int32_t)b;
+    const uint64_t d = (uint64_t)b - (uint64_t)bref;
+    far |= d + (1ull << 30) >= (1ull << 31);
+    return (int32_t)(uint32_t)d;
   };
-
-  // the halo lies inside the grid: no neighbour needs a bounds check
-  const bool inner = c.z0 - G::ZO >= 0 && c.z0 + TZ - 1 + G::ZO < box.nz && c.y0 >= 1 &&
-                     c.y0 + TY < box.ny && c.x0 >= 1 && c.x0 + TX < box.nx;
-  // per owned point: mk = same bin and lower (the flags), up = same bin and
-  // higher (the neighbours whose relaxation depends on this point)
-  uint16_t mk[G::PER], up[G::PER];
+  __syncthreads();  // lds.wide
+  int32_t bo[PZ];
 #pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    const int i = threadIdx.x + k * kThreads;
-    const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-    const int z = c.z0 + iz, y = c.y0 + iy, xx = c.x0 + ix;
-    uint32_t sm = 0, lm = 0;
-    const int li = G::local(i);
-    const Key kp = key_at(li);
-    const int64_t bp = bin_at(li);  // float64: low 32 bits
-    // float64: the whole bin (from its low bits and the halo's lowest bin,
-    // or re-quantized when the halo is wide)
-    int64_t bfull = bp;
-    if constexpr (K == 8)
-      bfull = wide ? Tr::q(Tr::to_double(Tr::unkey(kp)), prm->inv)
-                   : bref + (int64_t)(uint32_t)((uint32_t)bp - (uint32_t)bref);
-    if (z < box.nz && y < box.ny && xx < box.nx)  // for the encoder
-      bins[((int64_t)z * box.ny + y) * box.nx + xx] = (Bin)bfull;
-    if (inner) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int ln = li + kOff[j][0] * (G::HY * G::HX) + kOff[j][1] * G::HX + kOff[j][2];
-        const Key kq = key_at(ln);
-        // branch-free: same bin, and lower in (value, index) order
-        const bool lower = (kq < kp) | ((kq == kp) & ((j & 1) != 0));
-        sm |= (uint32_t)(bin_at(ln) == bp) << j;
-        lm |= (uint32_t)lower << j;
-      }
-      if (K == 8 && wide) sm = wide_same<K, TZ, TY, TX>(Pk, li, bfull, prm->inv, z, y, xx, box);
-      mask[((int64_t)z * box.ny + y) * box.nx + xx] = (uint16_t)(sm & lm);
-    } else if (z < box.nz && y < box.ny && xx < box.nx) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        int zz = z + kOff[j][0], yy = y + kOff[j][1], xq = xx + kOff[j][2];
-        if (zz < 0 || zz >= box.nz || yy < 0 || yy >= box.ny || xq < 0 || xq >= box.nx)
-          continue;
-        const int ln = li + kOff[j][0] * (G::HY * G::HX) + kOff[j][1] * G::HX + kOff[j][2];
-        const Key kq = key_at(ln);
-        // odd j: the neighbour has the lower index
-        const bool lower = (kq < kp) | ((kq == kp) & ((j & 1) != 0));
-        sm |= (uint32_t)(bin_at(ln) == bp) << j;
-        lm |= (uint32_t)lower << j;
-      }
-      if (K == 8 && wide) sm = wide_same<K, TZ, TY, TX>(Pk, li, bfull, prm->inv, z, y, xx, box);
-      mask[((int64_t)z * box.ny + y) * box.nx + xx] = (uint16_t)(sm & lm);
-    }
-    mk[k] = (uint16_t)(sm & lm);
-    up[k] = (uint16_t)(sm & ~lm);
+  for (int k = 0; k < PZ; ++k) {
+    bad_v |= !Tr::finite(u[k]);
+    const int64_t b = first_bin<K>(Tr::to_double(u[k]), inv, bad_r);
+    bo[k] = in(k) ? low(b) : kNoBin;
+    if (in(k)) bins[g0 + k * gstep] = (typename Tr::Bin)b;  // for the encoder
+    lds.x[li0 + k * G::kSlot] = u[k];
+    B[li0 + k * G::kSlot] = bo[k];
   }
+#pragma unroll
+  for (int q = 0; q < F::kPer; ++q) {
+    const int64_t b = first_bin<K>(Tr::to_double(hu[q]), inv, bad_r);
+    const int32_t lb = (hin >> q) & 1u ? low(b) : kNoBin;
+    if (hl[q] >= 0) {
+      lds.x[hl[q]] = hu[q];
+      B[hl[q]] = lb;
+    }
+  }
+  if (bad_v) set_status(prm, ST_NONFINITE);
+  if (bad_r) set_status(prm, ST_RANGE);
+  if (K == 8 && __ballot(far) && lane() == 0) lds.wide = 1;
   __syncthreads();
-  // halo subbins: 0, or (hc >= 0) those of the neighbour tiles of colour hc,
-  // final from an earlier launch
-  if (TZ > 1 && hc >= 0) {
-    // loads in flight four at a time (points not taken read point 0)
+  const bool wide = K == 8 && lds.wide;
+  // order flags: same bin and lower in (value, index) order
+  uint16_t mk[PZ];
 #pragma unroll
-    for (int q0 = 0; q0 < HL; q0 += 4) {
-    uint32_t hv[4];
+  for (int k = 0; k < PZ; ++k) {
+    const int li = li0 + k * G::kSlot;
+    const Val vp = val(u[k]);
+    uint32_t m = 0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int q = q0 + r;
-      const int i = threadIdx.x + q * kThreads;
-      const int hz = i / (G::HY * G::HX), hy = (i / G::HX) % G::HY, hx = i % G::HX;
-      const int z = c.z0 + hz - G::ZO, y = c.y0 + hy - 1, xx = c.x0 + hx - 1;
-      const bool own = hz >= G::ZO && hz < G::ZO + TZ && hy >= 1 && hy <= TY && hx >= 1 &&
-                       hx <= TX;
-      const bool take = i < G::H && !own && z >= 0 && z < box.nz && y >= 0 && y < box.ny &&
-                        xx >= 0 && xx < box.nx &&
-                        tile_colour(z / TZ, y / TY, xx / TX) == (uint32_t)hc;
-      const uint32_t v = sub[take ? ((int64_t)z * box.ny + y) * box.nx + xx : 0];
-      hv[r] = take ? v : 0u;
+    for (int j = NJ - 1; j >= 0; --j) {
+      const int ln = li + kOff[j][0] * HXY + kOff[j][1] * G::HX + kOff[j][2];
+      const Val vq = X[ln];
+      // odd j: the neighbour has the lower index
+      m = shift_in(m, __ballot(B[ln] == bo[k]), __ballot((j & 1) ? vq <= vp : vq < vp));
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = threadIdx.x + (q0 + r) * kThreads;
-      if (i < G::H) S[i] = hv[r];
-    }
-    }
-  } else {
-    for (int i = threadIdx.x; i < G::H; i += kThreads) {
-      uint32_t v = 0;
-      if (hc >= 0) {  // 2D tiles: one load at a time (fewer registers)
-        const int hy = i / G::HX, hx = i % G::HX;
-        const int y = c.y0 + hy - 1, xx = c.x0 + hx - 1;
-        const bool own = hy >= 1 && hy <= TY && hx >= 1 && hx <= TX;
-        if (!own && y >= 0 && y < box.ny && xx >= 0 && xx < box.nx &&
-            tile_colour(c.z0, y / TY, xx / TX) == (uint32_t)hc)
-          v = sub[((int64_t)c.z0 * box.ny + y) * box.nx + xx];
+    if (wide && in(k)) {
+      uint32_t lm = 0;
+      const int z = c.z0 + (TZ > 1 ? k : 0), y = c.y0 + iy + (TZ > 1 ? 0 : k * kRows),
+                xx = c.x0 + ix;
+#pragma unroll 1
+      for (int j = 0; j < NJ; ++j) {
+        const int zz = z + off_z(j), yy = y + off_y(j), xq = xx + off_x(j);
+        if (zz < 0 || zz >= box.nz || yy < 0 || yy >= box.ny || xq < 0 || xq >= box.nx) continue;
+        const Val vq = X[li + off_lin(j, G::HX, HXY)];
+        const bool same = q_bin((double)vq, inv) == q_bin((double)vp, inv);
+        lm |= (uint32_t)(same && (vq < vp || (vq == vp && (j & 1)))) << j;
       }
-      S[i] = v;
+      m = lm;
+    }
+    mk[k] = in(k) ? (uint16_t)m : (uint16_t)0;
+    if (in(k)) mask[g0 + k * gstep] = (uint16_t)m;
+    if constexpr (TZ > 1) {
+      P[li] = kNoFlags & ~((uint32_t)mk[k] << 16);
+    } else {
+      // the count of lower neighbours inside the tile
+      const int ry = iy + k * kRows;
+      const uint32_t inb = (ry == 0 ? ~0x28u : ~0u) & (ry == TY - 1 ? ~0x14u : ~0u) &
+                           (ix == 0 ? ~0x22u : ~0u) & (ix == TX - 1 ? ~0x11u : ~0u);
+      P[li] = ((0x3fu & ~(uint32_t)mk[k]) << 16) |
+              (uint32_t)__popc(mk[k] & inb) << kLeftShift;
     }
   }
-  __syncthreads();
-  uint8_t* lvb = nullptr;
-  if constexpr (TZ == 1) {
-    const int nlev = kahn_relax<TZ, TY, TX>(S, buf + G::H * 4, mk, up, lvb);
-    if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)(nlev + 1));
+#pragma unroll
+  for (int q = 0; q < F::kPer; ++q)
+    if (hl[q] >= 0) P[hl[q]] = kNoFlags | kHalo | hs[q];
+  for (int i = threadIdx.x; i < Blind<TZ, TY, TX>::kCells; i += kThreads)
+    P[Blind<TZ, TY, TX>::cell(i)] = kNoFlags | kHalo;
+  // (a first run's subbins stay below twice the points of a tile: 16 bits)
+  if constexpr (TZ > 1) {
+    relax<TZ, TY, TX, K == 8>(P, lds.E, mk, counters, itot, t);
   } else {
-    relax<TZ, TY, TX, K == 8>(S, mk, counters, itot, t);
+    const int levels = peel<TZ, TY, TX>(P, lds.E.list, &lds.E.tail);
+    if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)(levels + 1));
   }
+#pragma unroll
+  for (int k = 0; k < PZ; ++k)
+    if (in(k)) sub[g0 + k * gstep] = P[li0 + k * G::kSlot] & 0xffffu;
   uint32_t dirs = 0;
 #pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    const int i = threadIdx.x + k * kThreads;
-    const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-    const int z = c.z0 + iz, y = c.y0 + iy, xx = c.x0 + ix;
-    if (z < box.nz && y < box.ny && xx < box.nx) {
-      const uint32_t v = S[G::local(i)];
-      const int64_t g = ((int64_t)z * box.ny + y) * box.nx + xx;
-      sub[g] = v;
-      if (TZ == 1 && tl.lev) tl.lev[g] = lvb[i];
-      if (v && up[k]) dirs |= out_dirs<TZ, TY, TX>(i, up[k]);
+  for (int q = 0; q < F::kPer; ++q) {
+    if (w + q * kWaves >= F::kSlots) continue;
+    const FaceSlot& f = kFaces<TZ, TY, TX>.s[w + q * kWaves];
+    const bool on = (hin >> q) & 1u;
+    const int l = on ? hl[q] : f.li;
+    // a target's subbin above th raises the point beyond what it has (what
+    // its tile took from a subbin of 0 it already has); the target has the
+    // higher index, weight 1, on low faces
+    const uint32_t wt = 1u - f.weight;
+    const uint32_t th = !on ? 0xffffu : hs[q] > wt ? hs[q] - wt : 0u;
+    uint64_t up[F::ND], any = 0;
+#pragma unroll
+    for (int k = 0; k < F::ND; ++k) {
+      up[k] = __ballot((P[l + f.d[k]] & (0xffffu | kHalo)) - th - 1u < 0xffffu);
+      any |= up[k];
     }
+    if (!any) continue;
+    const Val vh = val(hu[q]);
+    const int32_t bh = B[l];
+    any = 0;
+#pragma unroll
+    for (int k = 0; k < F::ND; ++k) {
+      const Val vq = X[l + f.d[k]];
+      const uint64_t lt = __ballot(vq < vh), le = __ballot(vq <= vh);
+      uint64_t same = __ballot(B[l + f.d[k]] == bh);
+      if (wide) same = __ballot(q_bin((double)vq, inv) == q_bin((double)vh, inv));
+      any |= up[k] & (f.weight ? le : lt) & same;
+    }
+    if ((any >> lane()) & 1u) dirs |= cell_dir<TZ, TY, TX>(l);
   }
-  return block_or32(dirs);
+  if (__ballot(dirs != 0u)) {
+    dirs = wave_reduce(dirs, OpOr{});
+    if (lane() == 0) atomicOr(&lds.dirs, dirs);
+  }
+  __syncthreads();
+  return lds.dirs;
 }
+
+// Waves per SIMD the first pass is held to (its register budget).
+template <int K, int TZ, int TY, int TX>
+constexpr int kTile0Waves = TZ * TY * TX > 1024 && TZ > 1 ? (K == 4 ? 3 : 2) : K == 4 ? 5 : TZ > 1 ? 4 : 3;
 
 // Q.q null: mark the tiles to sweep next (and append them to the work list
 // of sweep 1 when lists is given); else list them in the repair queue (the
 // kernel boundary publishes the subbins).
 template <int K, int TZ, int TY, int TX>
-__global__ __launch_bounds__(kThreads) void k_tile0(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kTile0Waves<K, TZ, TY, TX>, 8))) void k_tile0(
     const typename Traits<K>::Raw* __restrict__ x, Box box, Tiling tl, Params* prm,
     typename Traits<K>::Bin* __restrict__ bins,
     uint16_t* __restrict__ mask, uint32_t* __restrict__ sub, uint32_t* stamp,
@@ -1337,149 +1509,204 @@ __global__ __launch_bounds__(kThreads) void k_tile0(
 
 // Later sweeps: tiles marked for this sweep reload their halo and relax.
 // One sweep of tile t if it is marked for it.  Returns (block-uniform) the
-// neighbour tiles holding a point whose flags name a changed boundary point
-// of this tile as a lower neighbour (0 if the tile did not run).
+// neighbour tiles holding a point that would rise from what changed in this
+// tile (0 if the tile did not run).
+// A run pushes the halo points into the tile (what changed since the tile's
+// last run can only have come from there), then each wave runs event rounds
+// from the points it raised.
 // QM (queue mode): the tile was taken from the repair queue, and other
 // workgroups change subbins while it runs, so subbins are read and written
 // as relaxed atomics at agent scope (coherent across the XCDs' L2 caches).
 // With `blockers` given, thread 0 stores there the higher-index
 // neighbour tiles holding a same-bin lower neighbour of one of the tile's
 // points (the tiles its run depends on; bits 14..26 of the 27-direction set).
-// LV: a 2D tile relaxes in the order of the levels kept by the first pass
-// (tl.lev), if any and all known; otherwise relaxation passes.
-template <int TZ, int TY, int TX, bool QM = false, bool LV = false>
-__device__ __forceinline__ uint32_t repair_body(Box box, Tiling tl, const uint16_t* __restrict__ mask,
-                            uint32_t* __restrict__ sub, const uint32_t* stamp,
-                            uint32_t* counters, unsigned long long* itot, uint32_t sweep,
-                            uint32_t t, TileCoord& c, uint32_t* blockers = nullptr) {
+// LDS of a run, handed in by the kernel (one buffer where it runs 2D and 3D
+// tiles).
+template <int TZ, int TY, int TX>
+struct RunLds {
+  uint32_t P[TileGeom<TZ, TY, TX>::H];  // LDS words (32-bit way: subbins)
+  EventLds<TZ * TY * TX> E;
+  uint32_t go;
+};
+template <int TZ, int TY, int TX, bool QM = false>
+__device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
+                            const uint16_t* __restrict__ mask, uint32_t* __restrict__ sub,
+                            const uint32_t* stamp, uint32_t* counters,
+                            unsigned long long* itot, uint32_t sweep, uint32_t t, TileCoord& c,
+                            uint32_t* blockers = nullptr) {
   using G = TileGeom<TZ, TY, TX>;
+  using F = Faces<TZ, TY, TX>;
   constexpr int NJ = TZ == 1 ? 6 : 14;
-  __shared__ uint32_t S[G::H];
-  __shared__ uint16_t M[G::H];  // flags of the halo and the owned points
+  constexpr int HXY = G::HY * G::HX;
+  uint32_t* const P = lds.P;
+  EventLds<G::NPT>& E = lds.E;
+  // flags of the halo and the owned points (32-bit way)
+  uint16_t* M = &E.list[0][0][0];
+  static_assert(sizeof(E.list) >= G::H * 2, "the flags fit the event lists");
   // one read decides for the whole block (a neighbour may raise the stamp
   // concurrently)
-  if constexpr (!QM) {
-    __shared__ uint32_t go;
-    if (threadIdx.x == 0) go = stamp[t] >= sweep;
-    __syncthreads();
-    if (!go) return 0;
-  }
-  c = tile_coord<TZ, TY, TX>(t, tl);
-  constexpr int HL = (G::H + kThreads - 1) / kThreads;
-  {
-    uint32_t hv[HL];
-    uint16_t hm[HL];
-    // every load issued unconditionally (points outside the grid or the
-    // halo read point 0 and are zeroed afterwards), so that all of them are
-    // in flight together instead of one wait per halo point
-    auto take = [&](int q, int64_t g, bool in) {
-      const uint32_t v =
-          QM ? __hip_atomic_load(sub + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : sub[g];
-      const uint16_t m = mask[g];
-      hv[q] = in ? v : 0u;
-      hm[q] = in ? m : (uint16_t)0;
-    };
-    // a halo inside the grid (most tiles): 32-bit offsets from the halo's
-    // first point, no bounds checks
-    const bool inner = c.z0 - G::ZO >= 0 && c.z0 + TZ - 1 + G::ZO < box.nz && c.y0 >= 1 &&
-                       c.y0 + TY < box.ny && c.x0 >= 1 && c.x0 + TX < box.nx &&
-                       (uint64_t)box.ny * (uint64_t)box.nx * G::HZ < (1ull << 31);
-    if (inner) {
-      const int64_t g0 = ((int64_t)(c.z0 - G::ZO) * box.ny + (c.y0 - 1)) * box.nx + (c.x0 - 1);
-      const uint32_t nyx = (uint32_t)box.ny * (uint32_t)box.nx;
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        const uint32_t hz = (uint32_t)i / (G::HY * G::HX), hy = ((uint32_t)i / G::HX) % G::HY,
-                       hx = (uint32_t)i % G::HX;
-        const bool in = i < G::H;
-        take(q, in ? g0 + (int64_t)(hz * nyx + hy * (uint32_t)box.nx + hx) : 0, in);
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < HL; ++q) {
-        const int i = threadIdx.x + q * kThreads;
-        const int hz = i / (G::HY * G::HX), hy = (i / G::HX) % G::HY, hx = i % G::HX;
-        const int z = c.z0 + hz - G::ZO, y = c.y0 + hy - 1, x = c.x0 + hx - 1;
-        const bool in = i < G::H && z >= 0 && z < box.nz && y >= 0 && y < box.ny && x >= 0 &&
-                        x < box.nx;
-        take(q, in ? ((int64_t)z * box.ny + y) * box.nx + x : 0, in);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < HL; ++q) {
-      const int i = threadIdx.x + q * kThreads;
-      if (i < G::H) {
-        S[i] = hv[q];
-        M[i] = hm[q];
-      }
-    }
+  if (threadIdx.x == 0) {
+    lds.go = QM || stamp[t] >= sweep;
+    E.big = 0;
+    E.over = 0;
+    E.dirs = 0;
   }
   __syncthreads();
-  uint16_t mk[G::PER];
-  uint32_t old[G::PER];
+  if (!lds.go) return 0;
+  c = tile_coord<TZ, TY, TX>(t, tl);
+  const int w = __builtin_amdgcn_readfirstlane(wave());
+  const int li0 = G::local(threadIdx.x);
+  const int64_t nyx = (int64_t)box.ny * box.nx;
+  const int64_t g00 = ((int64_t)c.z0 * box.ny + c.y0) * box.nx + c.x0;  // the tile's first point
+  uint32_t ov[G::PER], hv[F::kPer];
+  uint16_t om[G::PER], hm[F::kPer];
+  int hl[F::kPer];  // LDS index of the slot's point (-1: none)
+  int64_t og[G::PER];
+  bool wide;
+  {
+    // every load issued unconditionally (points outside the grid read the
+    // tile's first point and are zeroed afterwards), so that all of them are
+    // in flight together
+    auto take = [&](int64_t g, bool in, uint32_t& v, uint16_t& m) {
+      g = in ? g : g00;
+      v = QM ? __hip_atomic_load(sub + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : sub[g];
+      m = mask[g];
+      v = in ? v : 0u;
+      m = in ? m : (uint16_t)0;
+    };
 #pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    const int li = G::local(threadIdx.x + k * kThreads);
-    mk[k] = M[li];
-    old[k] = S[li];
-  }
-  int nlev = -1;
-  if constexpr (LV && TZ == 1) {
-    if (tl.lev) {
-      uint8_t lv[G::PER];
-#pragma unroll
-      for (int k = 0; k < G::PER; ++k) {
-        // a point with flags lies in the grid
-        const int i = threadIdx.x + k * kThreads;
-        lv[k] = mk[k] ? tl.lev[((int64_t)(c.y0 + i / TX)) * box.nx + c.x0 + i % TX] : 0;
-      }
-      nlev = level_relax<TZ, TY, TX>(S, mk, lv);
-    }
-  }
-  // four-slot 3D tiles relax with the masks spread over bytes (k_repair is
-  // held to six workgroups per CU for the registers that takes)
-  if (nlev < 0) relax<TZ, TY, TX, (TZ > 1 && G::PER <= 4)>(S, mk, counters, itot, t);
-  else if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)(nlev + 1));
-  uint32_t dirs = 0;
-#pragma unroll
-  for (int k = 0; k < G::PER; ++k) {
-    const int i = threadIdx.x + k * kThreads;
-    const int li = G::local(i);
-    const uint32_t v = S[li];
-    if (v != old[k]) {
+    for (int k = 0; k < G::PER; ++k) {
+      const int i = threadIdx.x + k * kThreads;
       const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-      uint32_t* dst = sub + ((int64_t)(c.z0 + iz) * box.ny + c.y0 + iy) * box.nx + c.x0 + ix;
-      if (QM) __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else *dst = v;
-      if (G::on_edge(i)) {
-        // halo neighbours whose flags name this point (offset j from here is
-        // offset j ^ 1 from there)
-        uint32_t dep = 0;
+      og[k] = g00 + iz * nyx + (int64_t)iy * box.nx + ix;
+      take(og[k], c.z0 + iz < box.nz && c.y0 + iy < box.ny && c.x0 + ix < box.nx, ov[k], om[k]);
+    }
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const int z = iz + kOff[j][0], y = iy + kOff[j][1], x = ix + kOff[j][2];
-          if (z < 0 || z >= TZ || y < 0 || y >= TY || x < 0 || x >= TX) {
-            const int ln = li + kOff[j][0] * (G::HY * G::HX) + kOff[j][1] * G::HX + kOff[j][2];
-            dep |= (uint32_t)((M[ln] >> (j ^ 1)) & 1u) << j;
-          }
-        }
-        if (dep) dirs |= out_dirs<TZ, TY, TX>(i, dep);
+    for (int q = 0; q < F::kPer; ++q) {
+      hl[q] = -1;
+      hv[q] = 0;
+      hm[q] = 0;
+      if (w + q * kWaves < F::kSlots) {
+        const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], c, box, g00);
+        take(f.g, f.in, hv[q], hm[q]);
+        hl[q] = f.li;
+      }
+    }
+    uint32_t top = 0;
+#pragma unroll
+    for (int k = 0; k < G::PER; ++k) {
+      P[li0 + k * G::kSlot] = (ov[k] | (uint32_t)om[k] << 16) ^ kNoFlags;
+      top = max(top, ov[k]);
+    }
+#pragma unroll
+    for (int q = 0; q < F::kPer; ++q) {
+      if (hl[q] >= 0) P[hl[q]] = (hv[q] | (uint32_t)hm[q] << 16) ^ (kNoFlags | kHalo);
+      top = max(top, hv[q]);
+    }
+    for (int i = threadIdx.x; i < Blind<TZ, TY, TX>::kCells; i += kThreads)
+      P[Blind<TZ, TY, TX>::cell(i)] = kNoFlags | kHalo;
+    if (__ballot(top > kPackMax) && lane() == 0) E.big = 1;
+    __syncthreads();
+    wide = E.big;
+  }
+  uint32_t dirs = 0, ups = 0;
+  if (wide) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < G::PER; ++k) {
+      P[li0 + k * G::kSlot] = ov[k];
+      M[li0 + k * G::kSlot] = om[k];
+    }
+#pragma unroll
+    for (int q = 0; q < F::kPer; ++q) {
+      if (hl[q] >= 0) {
+        P[hl[q]] = hv[q];
+        M[hl[q]] = hm[q];
+      }
+    }
+    __syncthreads();
+    relax_wide<TZ, TY, TX>(P, om, counters, itot, t);
+#pragma unroll
+    for (int k = 0; k < G::PER; ++k) {
+      const int i = threadIdx.x + k * kThreads;
+      const int li = G::local(i);
+      const uint32_t v = P[li];
+      if (QM && blockers && om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
+      if (v == ov[k]) continue;
+      if (QM) __hip_atomic_store(sub + og[k], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else sub[og[k]] = v;
+      if (!G::on_edge(i)) continue;
+      // halo neighbours whose flags name this point (offset j from here is
+      // offset j ^ 1 from there)
+      const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
+      uint32_t dep = 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int z = iz + kOff[j][0], y = iy + kOff[j][1], x = ix + kOff[j][2];
+        if (z < 0 || z >= TZ || y < 0 || y >= TY || x < 0 || x >= TX)
+          dep |= (uint32_t)((M[li + kOff[j][0] * HXY + kOff[j][1] * G::HX + kOff[j][2]] >>
+                             (j ^ 1)) & 1u) << j;
+      }
+      if (dep) dirs |= out_dirs<TZ, TY, TX>(i, dep);
+    }
+  } else {
+    // the face points push into the tile
+    uint32_t n = 0;
+#pragma unroll
+    for (int q = 0; q < F::kPer; ++q) {
+      if (w + q * kWaves >= F::kSlots) continue;
+      const FaceSlot& f = kFaces<TZ, TY, TX>.s[w + q * kWaves];
+      const uint32_t nv = hl[q] >= 0 ? hv[q] + f.weight : 0u;
+      const int l = hl[q] >= 0 ? hl[q] : f.li;
+      uint32_t x[F::ND], old[F::ND];
+#pragma unroll
+      for (int k = 0; k < F::ND; ++k) x[k] = P[l + f.d[k]];
+#pragma unroll
+      for (int k = 0; k < F::ND; ++k)
+        old[k] = raise_word(&P[l + f.d[k]], (x[k] & f.keep[k]) < nv, x[k], nv);
+#pragma unroll
+      for (int k = 0; k < F::ND; ++k) list_risen(E, E.list[w][0], n, old[k], l + f.d[k], nv);
+    }
+    int rounds = 1 + push_rounds<TZ, TY, TX>(P, E, n);
+    __syncthreads();
+    if (E.over) {
+      // some raised points were not listed: passes to the end, and every
+      // neighbour tile looks
+      rounds += word_passes<TZ, TY, TX>(P, E, counters);
+      dirs = 0x7ffffffu;
+    }
+    if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)rounds);
+    // the neighbour tiles whose halo points rose
+#pragma unroll
+    for (int q = 0; q < F::kPer; ++q) {
+      if (hl[q] >= 0 && P[hl[q]] >= (kHalo | kRose)) dirs |= cell_dir<TZ, TY, TX>(hl[q]);
+    }
+#pragma unroll
+    for (int k = 0; k < G::PER; ++k) {
+      const uint32_t wd = P[li0 + k * G::kSlot];
+      if (QM && blockers) {
+        const int i = threadIdx.x + k * kThreads;
+        if (om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
+      }
+      if (wd & kRose) {
+        if (QM)
+          __hip_atomic_store(sub + og[k], wd & 0xffffu, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        else sub[og[k]] = wd & 0xffffu;
       }
     }
   }
   if (QM && blockers) {
-    uint32_t ups = 0;
-#pragma unroll
-    for (int k = 0; k < G::PER; ++k) {
-      const int i = threadIdx.x + k * kThreads;
-      if (mk[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, mk[k]);
-    }
     const uint64_t both = block_or64((uint64_t)ups << 32 | dirs);
     if (threadIdx.x == 0) blockers[t] = (uint32_t)(both >> 32) & ~0x3fffu;
     return (uint32_t)both;
   }
-  return block_or32(dirs);
+  if (__ballot(dirs != 0u)) {
+    dirs = wave_reduce(dirs, OpOr{});
+    if (lane() == 0) atomicOr(&E.dirs, dirs);
+  }
+  __syncthreads();
+  return E.dirs;
 }
 
 // mark_neighbours for a sweep run colour by colour: a neighbour of the later
@@ -1525,7 +1752,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
   const uint32_t t = colour < 2 ? colour_tile(b, colour, tl) : b;
   if (t >= tl.ntiles) return;
   TileCoord c;
-  const uint32_t dirs = repair_body<TZ, TY, TX, false, true>(box, tl, mask, sub, stamp, counters,
+  __shared__ RunLds<TZ, TY, TX> lds;
+  const uint32_t dirs = repair_body<TZ, TY, TX>(lds, box, tl, mask, sub, stamp, counters,
                                                 relax_total(counters), sweep, t, c);
   if (!dirs) return;
   if (colour < 2) mark_neighbours_col(dirs, c, tl, stamp, counters, sweep, colour);
@@ -1548,8 +1776,9 @@ template <int TZ, int TY, int TX>
 __device__ __noinline__ uint32_t sweep_run(Box box, Tiling tl, const uint16_t* __restrict__ mask,
                                            uint32_t* __restrict__ sub, const uint32_t* stamp,
                                            uint32_t* counters, uint32_t sweep, uint32_t t) {
+  __shared__ RunLds<TZ, TY, TX> lds;
   TileCoord c;
-  return repair_body<TZ, TY, TX, false, true>(box, tl, mask, sub, stamp, counters, relax_total(counters),
+  return repair_body<TZ, TY, TX>(lds, box, tl, mask, sub, stamp, counters, relax_total(counters),
                                  sweep, t, c);
 }
 
@@ -1675,8 +1904,9 @@ template <int TZ, int TY, int TX>
 __device__ __noinline__ uint32_t repair_run(Box box, Tiling tl, const uint16_t* __restrict__ mask,
                                             uint32_t* __restrict__ sub, uint32_t* counters,
                                             uint32_t t, uint32_t* blockers) {
+  __shared__ RunLds<TZ, TY, TX> lds;
   TileCoord c;
-  return repair_body<TZ, TY, TX, true, true>(box, tl, mask, sub, nullptr, counters,
+  return repair_body<TZ, TY, TX, true>(lds, box, tl, mask, sub, nullptr, counters,
                                        relax_total(counters), 0, t, c, blockers);
 }
 
@@ -1822,12 +2052,15 @@ template <int S2, int S3>
 __device__ __forceinline__ uint32_t batch_repair_run(const Job& J, uint32_t* err,
                                                      unsigned long long* itot, uint32_t sweep,
                                                      uint32_t t, TileCoord& c) {
+  using L2 = RunLds<1, kTile2[S2][1], kTile2[S2][2]>;
+  using L3 = RunLds<kTile3[S3][0], kTile3[S3][1], kTile3[S3][2]>;
+  __shared__ __attribute__((aligned(16)))
+  uint8_t lds[sizeof(L2) > sizeof(L3) ? sizeof(L2) : sizeof(L3)];
   if (J.tl.tz == 1)
-    return repair_body<1, kTile2[S2][1], kTile2[S2][2]>(J.box, J.tl, J.mask, J.sub, J.stamp, err,
-                                                        itot, sweep, t, c);
-  return repair_body<kTile3[S3][0], kTile3[S3][1], kTile3[S3][2]>(J.box, J.tl, J.mask, J.sub,
-                                                                  J.stamp, err, itot, sweep, t,
-                                                                  c);
+    return repair_body<1, kTile2[S2][1], kTile2[S2][2]>(*(L2*)lds, J.box, J.tl, J.mask, J.sub,
+                                                        J.stamp, err, itot, sweep, t, c);
+  return repair_body<kTile3[S3][0], kTile3[S3][1], kTile3[S3][2]>(
+      *(L3*)lds, J.box, J.tl, J.mask, J.sub, J.stamp, err, itot, sweep, t, c);
 }
 
 // One sweep over the tiles listed for it, of fields of both tile shapes.
@@ -1875,7 +2108,8 @@ __global__ __launch_bounds__(kThreads) void k_params_d(const BatchDesc* bd, cons
 }
 
 template <int K, int TZ, int TY, int TX>
-__global__ __launch_bounds__(kThreads) void k_tile0_d(const BatchDesc* bd, const Job* jobs,
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kTile0Waves<K, TZ, TY, TX>, 8))) void k_tile0_d(const BatchDesc* bd, const Job* jobs,
                                                       int g) {
   const uint32_t it = bd->item0[PH_T][g] + xcd_tile(blockIdx.x, gridDim.x);
   const Job& J = jobs[find_job<&Job::t0>(jobs, (int)bd->job0[g], (int)bd->job0[g + 1], it)];
@@ -1889,7 +2123,7 @@ __global__ __launch_bounds__(kThreads) void k_tile0_d(const BatchDesc* bd, const
 // One sweep: workgroup b takes entry b of the sweep's work list (the grid
 // is the list's capacity; workgroups past its length exit at once).
 template <int S2, int S3>
-__global__ __launch_bounds__(kThreads) void k_repair_d(const BatchDesc* bd, const Job* jobs,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_repair_d(const BatchDesc* bd, const Job* jobs,
                                                        uint32_t sweep) {
   BatchCounters* bc = bd->bc;
   if (blockIdx.x >= bc->lens[sweep % kRing]) return;
