@@ -22,6 +22,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lopc_device.h"
 
@@ -379,8 +380,8 @@ __device__ void rze_decode_upper(const uint8_t* in, uint32_t in_len, uint32_t it
 // into registers (a byte's position among the kept bytes is a prefix count
 // over level 1) and counts their items; after the per-round counts are
 // exchanged, the same lanes fetch their units' payload.  Block barriers:
-// after the upper levels, after the round counts, after the payload, after
-// the plane mask.
+// after the upper levels, after the round counts, after the payload.  Units of
+// planes left out of sc.planes hold anything.
 template <int W>
 __device__ __forceinline__ bool rze_decode(const uint8_t* in, uint32_t in_len, uint32_t len,
                            uint64_t* U, Scratch& sc, uint32_t G) {
@@ -397,47 +398,57 @@ __device__ __forceinline__ bool rze_decode(const uint8_t* in, uint32_t in_len, u
   // level 1 as 64-bit words (bit q: level-0 byte q differs from the one
   // before); bits from n0 on do not count
   const uint64_t* l1 = (const uint64_t*)sc.lv1;
+  auto level1 = [&](uint32_t wi) -> uint64_t {
+    const uint64_t wd = l1[wi];
+    const uint32_t v = n0 - 64u * wi;
+    return v < 64 ? wd & ((1ull << v) - 1ull) : wd;
+  };
   uint32_t wexcl = 0, pos0 = pos1;
+  uint64_t live = ~0ull;  // rounds that may hold items
   if (top >= 1) {
     const uint32_t nw = (n0 + 63) / 64;  // <= 32
-    uint64_t wd = 0;
-    if ((uint32_t)lane() < nw) {
-      wd = l1[lane()];
-      const uint32_t v = n0 - 64u * (uint32_t)lane();
-      if (v < 64) wd &= (1ull << v) - 1ull;
-    }
+    const uint64_t wd = (uint32_t)lane() < nw ? level1((uint32_t)lane()) : 0ull;
     const uint32_t c = (uint32_t)__popcll(wd);
     const uint32_t inc = wave_scan_u32(c);
     wexcl = inc - c;
     pos0 = pos1 + (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     if (pos0 > in_len) return false;
+    // a round none of whose level-0 bytes differs from the one before it,
+    // after a zero byte, holds no items (most rounds: the bit planes above the
+    // highest set bit of the chunk); lane r looks at round r
+    constexpr uint32_t kB = 64 / W;  // level-0 bytes of a round
+    const uint32_t wi = (uint32_t)lane() / W, s0 = ((uint32_t)lane() % W) * kB;
+    const uint64_t rw = W == 1 ? wd : (uint64_t)__shfl((unsigned long long)wd, (int)wi, 64);
+    const uint32_t before =
+        (W == 1 ? wexcl : (uint32_t)__shfl((int)wexcl, (int)wi, 64)) +
+        (W == 1 ? 0u : (uint32_t)__popcll(rw & ((1ull << s0) - 1ull)));
+    const bool same = (uint32_t)lane() < rounds &&
+                      (W == 1 ? rw : (rw >> s0) & ((1ull << (kB & 63)) - 1ull)) == 0;
+    const uint32_t byte = same && before ? in[pos1 + before - 1] : 0u;
+    live = ~__ballot(same && byte == 0);
+    if (wave() == 0 && (uint32_t)lane() < rounds && !((live >> lane()) & 1u)) sc.rpre[lane()] = 0;
   }
+  if (threadIdx.x == 0) sc.planes = 0;
   uint32_t mi[kRPW], incl[kRPW];
+  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane(wave());
 #pragma unroll
   for (int k = 0; k < kRPW; ++k) {
-    const uint32_t r = wave() + kCW * k;
+    const uint32_t r = w0 + kCW * k;
     mi[k] = 0;
     incl[k] = 0;
-    if (r >= rounds) continue;
+    if (r >= rounds || !((live >> r) & 1u)) continue;
     const uint32_t u = r * 64 + lane();
-    // the level-1 word holding the bits of this round's level-0 bytes
-    // (r / W: one word per round of 8 / W items a unit) and the kept bytes
-    // before it
-    uint64_t wd = 0;
-    uint32_t wb = 0;
-    if (top >= 1) {
-      const uint32_t wi = r / W;
-      wd = l1[wi];
-      const uint32_t v = n0 - 64u * wi;
-      if (v < 64) wd &= (1ull << v) - 1ull;
-      wb = (uint32_t)__builtin_amdgcn_readlane((int)wexcl, (int)wi);
-    }
     if (u < NU) {
       const uint32_t q = W == 1 ? u : (W == 4 ? u / 4 : u / 8);  // its level-0 byte
       uint32_t b0;
       if (top == 0) {
         b0 = in[q];  // the top level is level 0 (q < n0 = its size)
       } else {
+        // the level-1 word holding the bits of this round's level-0 bytes
+        // (r / W: one word per round of 8 / W items a unit) and the kept bytes
+        // before it
+        const uint64_t wd = level1(r / W);
+        const uint32_t wb = (uint32_t)__builtin_amdgcn_readlane((int)wexcl, (int)(r / W));
         const uint32_t e = wb + (uint32_t)__popcll(wd & ((2ull << (q & 63)) - 1ull));
         b0 = e ? in[pos1 + e - 1] : 0u;
       }
@@ -452,35 +463,41 @@ __device__ __forceinline__ bool rze_decode(const uint8_t* in, uint32_t in_len, u
   const uint32_t rinc = wave_scan_u32(rc);
   const uint32_t npay = (uint32_t)__builtin_amdgcn_readlane((int)rinc, 63);
   if (pos0 + npay * W != in_len) return false;
+  // a round without items needs no zeros where nobody reads a plane left out
+  // of the mask: whole planes to a round
+  const bool blank = !G || (64u % G) != 0;
   uint64_t pm = 0;
 #pragma unroll
   for (int k = 0; k < kRPW; ++k) {
-    const uint32_t r = wave() + kCW * k;
+    const uint32_t r = w0 + kCW * k;
     if (r >= rounds) break;
     const uint32_t u = r * 64 + lane();
-    if (!__ballot(mi[k] != 0u)) {
-      if (u < NU) U[u] = 0;
+    if (!((live >> r) & 1u) || !__ballot(mi[k] != 0u)) {
+      if (blank && u < NU) U[u] = 0;
       continue;
     }
     const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)(rinc - rc), (int)r);
     const uint32_t m = mi[k];
     const uint32_t c = (uint32_t)__popc(m);
-    if (u >= NU) continue;
-    const uint64_t v = unit_payload<W>(in + pos0 + W * (base + incl[k] - c), m, c);
-    U[u] = v;
-    if (G && v) pm |= 1ull << (u / G);
+    uint64_t v = 0;
+    if (u < NU) {
+      v = unit_payload<W>(in + pos0 + W * (base + incl[k] - c), m, c);
+      U[u] = v;
+    }
+    if (G == 64) {
+      pm |= (uint64_t)(__ballot(v != 0) != 0) << r;
+    } else if (G == 32) {
+      const uint64_t b = __ballot(v != 0);
+      pm |= (uint64_t)((uint32_t)b != 0) << (2 * r) | (uint64_t)((b >> 32) != 0) << (2 * r + 1);
+    } else if (G && v) {
+      pm |= 1ull << (u / G);
+    }
   }
   if (G) {
-    pm = wave_reduce(pm, OpOr{});
-    if (lane() == 0) sc.orv[wave()] = pm;
+    if (G != 64 && G != 32) pm = wave_reduce(pm, OpOr{});
+    if (pm && lane() == 0) atomicOr((unsigned long long*)&sc.planes, (unsigned long long)pm);
   }
   __syncthreads();
-  if (G) {
-    uint64_t m = 0;
-    for (int w = 0; w < kCW; ++w) m |= sc.orv[w];
-    if (threadIdx.x == 0) sc.planes = m;
-    __syncthreads();
-  }
   return true;
 }
 
@@ -975,37 +992,92 @@ __global__ __launch_bounds__(kThreads) void k_sum_parts(const uint32_t* parts,
   }
 }
 
-// Lowest representable value of bin b (as an order key): start next to the
-// real lower edge (b - 1/2) / inv and step to the first value whose bin is b.
+// Lower edge of bin b: the key of the lowest value whose bin is b or above (the
+// bins are monotone in the value, so bin b holds the keys from its edge up to
+// the edge of b + 1, none if they are equal); kNoKey if the search fails.
 template <int K>
-__device__ __forceinline__ bool bin_floor_key(int64_t b, double inv,
-                                              double winv, int64_t& out) {
+constexpr typename Traits<K>::Bin kNoKey =
+    (typename Traits<K>::Bin)((uint64_t)1 << (8 * sizeof(typename Traits<K>::Bin) - 1));
+// By steps: from next to the real edge (b - 1/2) / inv to the first value whose
+// bin is b or above.
+template <int K>
+__device__ __noinline__ typename Traits<K>::Bin edge_walk(int64_t b, double inv, double c) {
   using Tr = Traits<K>;
-  if (b > Tr::kBinLimit || b < -Tr::kBinLimit) return false;
-  double c = ((double)b - 0.5) * winv;
   int64_t k;
   if (K == 4) {
-    float f = (float)c;
-    uint32_t u = __float_as_uint(f);
-    if (!finite32(u)) return false;
+    const uint32_t u = __float_as_uint((float)c);
+    if (!finite32(u)) return kNoKey<K>;
     k = key32(u);
   } else {
-    uint64_t u = (uint64_t)__double_as_longlong(c);
-    if (!finite64(u)) return false;
+    const uint64_t u = (uint64_t)__double_as_longlong(c);
+    if (!finite64(u)) return kNoKey<K>;
     k = key64(u);
   }
   int steps = 0;
   while (k > -Tr::kMaxKey && Tr::q(Tr::to_double(Tr::unkey(k - 1)), inv) >= b) {
     --k;
-    if (++steps > 8) return false;
+    if (++steps > 8) return kNoKey<K>;
   }
   while (Tr::q(Tr::to_double(Tr::unkey(k)), inv) < b) {
-    if (k >= Tr::kMaxKey || ++steps > 8) return false;
+    if (k >= Tr::kMaxKey || ++steps > 8) return kNoKey<K>;
     ++k;
   }
-  if (Tr::q(Tr::to_double(Tr::unkey(k)), inv) != b) return false;
-  out = k;
-  return true;
+  return (typename Tr::Bin)k;
+}
+// Directly where rounding cannot blur it.  The real edge is at most 2^-51 |c|
+// from c = RN((b - 1/2) winv).  float32: values are 2^-24 apart, so the value
+// next to c on the far side of the edge is known unless c lies within 2^-50 of
+// a value.  float64: a value x reaches the bin iff x inv > b - 1/2, the sign of
+// one fma; the four values around c bracket the edge.  A tie or no bracket
+// goes by steps.  About 15 (float32) and 40 (float64) vector instructions an
+// edge; quantizing the candidates took 120 and 170, a quarter of the decoder's
+// instructions on a 1800 x 3600 float32 field (316 of 1351 per wave).
+template <int K>
+__device__ __forceinline__ typename Traits<K>::Bin lower_edge(int64_t b, double inv,
+                                                              double winv) {
+  const double h = (double)b - 0.5;
+  const double c = h * winv;
+  if constexpr (K == 4) {
+    const float f = (float)c;
+    const uint32_t u = __float_as_uint(f);
+    const double d = (double)f - c;
+    if (finite32(u) && fabs(d) > fabs(c) * 8.8817841970012523e-16)  // 2^-50
+      return (int32_t)key32(u) + (d < 0.0);
+  } else {
+    const uint64_t u = (uint64_t)__double_as_longlong(c);
+    const uint64_t mag = u & 0x7fffffffffffffffull;
+    if (mag >= 8 && mag < 0x7fe0000000000000ull && fabs(h) < 2251799813685248.0) {
+      const int64_t step = (int64_t)u < 0 ? -1 : 1;
+      uint32_t below = 0;
+      bool tie = false;
+#pragma unroll
+      for (int i = -2; i < 2; ++i) {
+        const double r = fma(__longlong_as_double((int64_t)u + i * step), inv, -h);
+        below += r < 0.0;
+        tie |= r == 0.0;
+      }
+      if (!tie && below - 1u < 3u) return key64(u) - 2 + (int64_t)below;
+    }
+  }
+  return edge_walk<K>(b, inv, c);
+}
+
+// The value of subbin s above lower edge t of bin b, and whether it exists and
+// lies in the bin (next: the edge of bin b + 1).
+template <int K>
+__device__ __forceinline__ bool point_ok(int64_t b, uint64_t s, typename Traits<K>::Bin t,
+                                         typename Traits<K>::Bin next, double inv,
+                                         typename Traits<K>::Raw& v) {
+  using Tr = Traits<K>;
+  v = 0;
+  // the room above t can exceed the int64 range: unsigned difference
+  if (b > Tr::kBinLimit || b < -Tr::kBinLimit || t == kNoKey<K> ||
+      (int64_t)t > Tr::kMaxKey || s > (uint64_t)Tr::kMaxKey - (uint64_t)(int64_t)t)
+    return false;
+  v = Tr::unkey((int64_t)t + (int64_t)s);
+  // inside bin b iff below the edge of bin b + 1
+  if (next != kNoKey<K>) return s < (uint64_t)((int64_t)next - (int64_t)t);
+  return Tr::q(Tr::to_double(v), inv) == b;
 }
 
 // copy n bytes from global src (4-byte aligned base) to LDS dst
@@ -1028,39 +1100,118 @@ __device__ __forceinline__ void stage(uint8_t* dst, const uint8_t* src, uint32_t
   }
 }
 
-// BIT_K inverse of the groups g = wave + kCW * i (i < GPW) of G into w[i]
-// (word 64g + lane): bit j of w[i] is bit `lane` of unit j * G + g, for the
-// planes j of mask pm (the others are zero).  Planes outer, groups inner: the
-// reads of one plane sit at fixed distances from one address, so they pair
-// up into two-address LDS reads.
-template <typename Word, int GPW>
-__device__ __forceinline__ void planes_to_words(const uint64_t* planes, uint32_t G, uint64_t pm,
-                                                Word (&w)[GPW]) {
-  const uint32_t* P32 = (const uint32_t*)planes;
-  const uint32_t half = (uint32_t)lane() >> 5, sh = (uint32_t)lane() & 31;
+// Byte c of w from byte i of t (the other bytes of w stay).
+template <int C, int I>
+__device__ __forceinline__ void put_byte(uint32_t& w, uint32_t t) {
+#define LOPC_PUT(c, i)                                                                     \
+  if constexpr (C == c && I == i)                                                          \
+    asm("v_mov_b32_sdwa %0, %1 dst_sel:BYTE_" #c " dst_unused:UNUSED_PRESERVE src0_sel:BYTE_" #i \
+        : "+v"(w) : "v"(t))
+#define LOPC_PUT4(c) LOPC_PUT(c, 0); LOPC_PUT(c, 1); LOPC_PUT(c, 2); LOPC_PUT(c, 3)
+  LOPC_PUT4(0);
+  LOPC_PUT4(1);
+  LOPC_PUT4(2);
+  LOPC_PUT4(3);
+#undef LOPC_PUT4
+#undef LOPC_PUT
+}
+// bits of the four 4 x 4 blocks' rows (bytes) and columns exchanged, twice per
+// byte: steps of an 8 x 8 bit transpose inside half a matrix
+__device__ __forceinline__ uint32_t transpose4(uint32_t x) {
+  uint32_t t = (x ^ (x >> 7)) & 0x00aa00aau;
+  x ^= t ^ (t << 7);
+  t = (x ^ (x >> 14)) & 0x0000ccccu;
+  return x ^ t ^ (t << 14);
+}
+// bit b (0..3) of m as byte b of all ones
+__device__ __forceinline__ uint32_t byte_mask(uint32_t m) {
+  const uint32_t y = ((m & 0xfu) * 0x00204081u) & 0x01010101u;
+  return (y << 8) - y;
+}
+// byte C of the PER words w from planes 8C .. 8C + 7 (mask pm, the others
+// zero) of G groups at `planes`
+template <int K, int C, int PER>
+__device__ __forceinline__ void plane_bytes(const uint8_t* planes, uint32_t G, uint64_t pm,
+                                            uint32_t (&lo)[PER], uint32_t (&hi)[PER]) {
+  const uint32_t bits = (uint32_t)(pm >> (8 * C)) & 0xffu;
+  if (!bits) return;  // uniform
+  const uint8_t* p = planes + (size_t)(8 * C) * G * 8 + (K == 4 ? threadIdx.x : threadIdx.x >> 1);
+  uint32_t b[8];
 #pragma unroll
-  for (int i = 0; i < GPW; ++i) w[i] = 0;
-  if (wave() + kCW * (GPW - 1) < G) {  // every group of this wave present
-    while (pm) {
-      const uint32_t j = (uint32_t)__builtin_ctzll(pm);
-      pm &= pm - 1;
-      const uint32_t* row = P32 + 2 * (j * G + wave()) + half;
-#pragma unroll
-      for (int i = 0; i < GPW; ++i) w[i] |= (Word)((row[2 * kCW * i] >> sh) & 1u) << j;
-    }
+  for (int j = 0; j < 8; ++j) b[j] = p[j * (G * 8)];
+  uint32_t x = b[0] | b[1] << 8 | b[2] << 16 | b[3] << 24;
+  uint32_t y = b[4] | b[5] << 8 | b[6] << 16 | b[7] << 24;
+  x &= byte_mask(bits);
+  y &= byte_mask(bits >> 4);
+  uint32_t(&w)[PER] = C < 4 ? lo : hi;
+  constexpr int D = C & 3;
+  if constexpr (K == 4) {
+    // rows: planes, columns: the eight words
+    x = transpose4(x);
+    y = transpose4(y);
+    const uint32_t l = (x & 0x0f0f0f0fu) | ((y << 4) & 0xf0f0f0f0u);
+    const uint32_t h = ((x >> 4) & 0x0f0f0f0fu) | (y & 0xf0f0f0f0u);
+    put_byte<D, 0>(w[0], l);
+    put_byte<D, 1>(w[1], l);
+    put_byte<D, 2>(w[2], l);
+    put_byte<D, 3>(w[3], l);
+    put_byte<D, 0>(w[4], h);
+    put_byte<D, 1>(w[5], h);
+    put_byte<D, 2>(w[6], h);
+    put_byte<D, 3>(w[7], h);
   } else {
-    while (pm) {
-      const uint32_t j = (uint32_t)__builtin_ctzll(pm);
-      pm &= pm - 1;
-      const uint32_t* row = P32 + 2 * (j * G + wave()) + half;
+    // the four words are half of each plane byte
+    const uint32_t sh = (threadIdx.x & 1u) * 4;
+    x = ((x >> sh) & 0x0f0f0f0fu) | ((y >> sh) & 0x0f0f0f0fu) << 4;
+    x = transpose4(x);
+    put_byte<D, 0>(w[0], x);
+    put_byte<D, 1>(w[1], x);
+    put_byte<D, 2>(w[2], x);
+    put_byte<D, 3>(w[3], x);
+  }
+}
+// BIT_K inverse of a chunk: thread t gets its PER consecutive words t * PER ..
+// (zero past the G groups).  Plane j holds bit j of word 64g + i as bit i of
+// unit j * G + g, so a thread's words are a byte (K = 4) or half a byte (K = 8)
+// of each plane: eight planes are read as eight bytes (neighbouring threads,
+// neighbouring bytes) and transposed in registers, about 45 (25) vector
+// instructions for 8 x 8 (8 x 4) bits instead of two per bit, and a chunk's
+// prefix sum needs one wave scan instead of one per group.
+template <int K, int PER>
+__device__ __forceinline__ void planes_to_words(const uint64_t* planes, uint32_t G, uint64_t pm,
+                                                typename Traits<K>::Word (&w)[PER]) {
+  uint32_t lo[PER], hi[PER];
 #pragma unroll
-      for (int i = 0; i < GPW; ++i)
-        if (wave() + kCW * i < G) w[i] |= (Word)((row[2 * kCW * i] >> sh) & 1u) << j;
+  for (int i = 0; i < PER; ++i) lo[i] = hi[i] = 0;
+  pm = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)pm) |
+       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(pm >> 32)) << 32;
+  if (threadIdx.x < (K == 4 ? G * 8 : G * 16)) {
+    const uint8_t* p = (const uint8_t*)planes;
+    plane_bytes<K, 0, PER>(p, G, pm, lo, hi);
+    plane_bytes<K, 1, PER>(p, G, pm, lo, hi);
+    plane_bytes<K, 2, PER>(p, G, pm, lo, hi);
+    plane_bytes<K, 3, PER>(p, G, pm, lo, hi);
+    if constexpr (K == 8) {
+      plane_bytes<K, 4, PER>(p, G, pm, lo, hi);
+      plane_bytes<K, 5, PER>(p, G, pm, lo, hi);
+      plane_bytes<K, 6, PER>(p, G, pm, lo, hi);
+      plane_bytes<K, 7, PER>(p, G, pm, lo, hi);
     }
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if constexpr (K == 4) w[i] = lo[i];
+    else w[i] = (uint64_t)lo[i] | (uint64_t)hi[i] << 32;
   }
 }
 
 // Decodes chunk c of a field (Sec. IV-E); a malformed record sets FORMAT.
+// Bound by vector issue (0.6 of the chip's rate) and the chunk's serial chain
+// (record, bitmap levels, prefix, edges; four chunks of eight waves fill a
+// CU).  Rounds without items are left out of the RZE stages, planes become
+// words by byte transposes, edges come from one comparison: 256^3 float32
+// 125 -> 100 us (vector instructions 1853 -> 1081 per wave), 512^3 float64 1422
+// -> 1113 us (1396 -> 834).
 template <int K>
 __device__ __forceinline__ void decode_body(const uint8_t* __restrict__ stream, uint32_t n,
                             const uint64_t* __restrict__ offsets, Params* prm,
@@ -1069,12 +1220,14 @@ __device__ __forceinline__ void decode_body(const uint8_t* __restrict__ stream, 
   using Tr = Traits<K>;
   using Word = typename Tr::Word;
   constexpr uint32_t W = kChunkBytes / K;
-  constexpr int GPW = (int)(W / 64 / kCW);  // groups per wave
+  constexpr int PER = (int)(W / kCT);  // consecutive points of a thread
   __shared__ uint64_t U[kMaxUnits + 2];
   __shared__ uint64_t Mb[kMaxUnits + 2];
   __shared__ Scratch sc;
-  __shared__ uint64_t gsum[64 + 1];  // per-group sums of the bin deltas
-  __shared__ int64_t s_mm[2][kCW];     // per-wave least / greatest bin
+  __shared__ uint64_t wsum[kCW];     // per-wave sums of the bin deltas
+  __shared__ uint64_t s_first;       // the chunk's first bin
+  __shared__ uint32_t s_mm[2][kCW];  // per-wave least / greatest bin, from the first - 2^30
+  __shared__ uint32_t s_far;         // some bin is 2^30 or more from the first
   __shared__ int s_bad;
 
   const uint32_t p0 = c * W, nc = min(W, n - p0);
@@ -1085,7 +1238,10 @@ __device__ __forceinline__ void decode_body(const uint8_t* __restrict__ stream, 
   // set the flag concurrently)
   const uint32_t rsize = ((const uint32_t*)(stream + kHeaderBytes))[c];
   const uint64_t roff = offsets[c];
-  if (threadIdx.x == 0) s_bad = 0;
+  if (threadIdx.x == 0) {
+    s_bad = 0;
+    s_far = 0;
+  }
   __shared__ uint32_t s_fail;
   if (threadIdx.x == 0) s_fail = prm->status & ST_FORMAT;
   __syncthreads();
@@ -1141,46 +1297,54 @@ __device__ __forceinline__ void decode_body(const uint8_t* __restrict__ stream, 
     if (threadIdx.x == 0) set_status(prm, ST_FORMAT);
     return;
   }
-  Word wv[GPW];
-  int64_t bmin = INT64_MAX, bmax = INT64_MIN;
+  // bins of the thread's points, each wave's first relative to the wave
+  Word wv[PER];
+  const uint32_t j0 = threadIdx.x * PER;
+  const bool full = nc == W;
   {
-    planes_to_words<Word, GPW>(planes, G, pm0, wv);
+    planes_to_words<K, PER>(planes, G, pm0, wv);
     const Word Mk = (Word)0xAAAAAAAAAAAAAAAAull;
+    Word run = 0;
 #pragma unroll
-    for (int i = 0; i < GPW; ++i) {
-      const uint32_t g = wave() + kCW * i;
-      const Word w = wv[i];
-      // negabinary -> delta; inclusive prefix within the group of 64 words
-      Word d = (g * 64 + lane() < nc) ? (Word)((w ^ Mk) - Mk) : (Word)0;
-      d = wave_scan<Word>(d);
-      wv[i] = d;
-      if (lane() == 63 && g < G) gsum[g] = (uint64_t)d;
+    for (int i = 0; i < PER; ++i) {
+      // negabinary -> delta; inclusive prefix within the thread
+      Word d = (Word)((wv[i] ^ Mk) - Mk);
+      if (!full && j0 + i >= nc) d = 0;
+      run += d;
+      wv[i] = run;
     }
+    const Word inc = wave_scan<Word>(run), exc = inc - run;
+    if (lane() == 63) wsum[wave()] = (uint64_t)inc;
+    if (threadIdx.x == 0) s_first = (uint64_t)wv[0];
     __syncthreads();
-    if (threadIdx.x < 64) {
-      uint64_t v = threadIdx.x < G ? gsum[threadIdx.x] : 0ull;
-      const uint64_t x = wave_scan_u64(v);
-      if (threadIdx.x < G) gsum[threadIdx.x] = x - v;  // exclusive
-    }
-    __syncthreads();
+    Word base = exc;
+    const int w0 = __builtin_amdgcn_readfirstlane(wave());
 #pragma unroll
-    for (int i = 0; i < GPW; ++i) {
-      const uint32_t g = wave() + kCW * i;
-      if (g < G) wv[i] += (Word)gsum[g];
-      const int64_t b = K == 4 ? (int64_t)(int32_t)(uint32_t)wv[i] : (int64_t)(uint64_t)wv[i];
-      if (g * 64 + lane() < nc) {
-        bmin = b < bmin ? b : bmin;
-        bmax = b > bmax ? b : bmax;
-      }
+    for (int w = 0; w < kCW - 1; ++w)
+      if (w0 > w) base += (Word)wsum[w];
+    // the chunk's bin range (for the edge table below), as distances from its
+    // first bin plus 2^30; the wave results are read after the next barrier
+    const Word first = (Word)s_first - (Word)(1u << 30);
+    uint32_t lo = 0xffffffffu, hi = 0;
+    bool far = false;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      wv[i] += base;
+      const Word off = wv[i] - first;
+      const bool on = full || j0 + i < nc;
+      if (K == 8) far |= on && (off >> 31) != 0;
+      const uint32_t o = (uint32_t)off;
+      lo = on && o < lo ? o : lo;
+      hi = on && o > hi ? o : hi;
     }
-    // the chunk's bin range (for the floor table below); the wave results
-    // are read after the next barrier
-    bmin = wave_reduce(bmin, OpMin{});
-    bmax = wave_reduce(bmax, OpMax{});
+    far |= (hi >> 31) != 0;
+    lo = wave_reduce(lo, OpMin{});
+    hi = wave_reduce(hi, OpMax{});
     if (lane() == 0) {
-      s_mm[0][wave()] = bmin;
-      s_mm[1][wave()] = bmax;
+      s_mm[0][wave()] = lo;
+      s_mm[1][wave()] = hi;
     }
+    if (__ballot(far) && lane() == 0) s_far = 1;
   }
 
   // subbins: RZE_1 -> RZE_K -> BIT_K (the part goes to U, free now)
@@ -1222,67 +1386,67 @@ __device__ __forceinline__ void decode_body(const uint8_t* __restrict__ stream, 
     if (threadIdx.x == 0) set_status(prm, ST_FORMAT);
     return;
   }
-  // BIT_K inverse of the subbins into registers, word 64g + lane of group
-  // g = wave + kCW * i in sv[i] (as the bins)
-  Word sv[GPW];
-  planes_to_words<Word, GPW>(planes, G, spm, sv);
+  Word sv[PER];
+  planes_to_words<K, PER>(planes, G, spm, sv);
 
-  // reconstruct (Sec. IV-E).  The bin floors of the chunk's bin range go to
-  // a table in the spare buffer when the range is small enough, so that each
-  // distinct bin is walked once.
+  // reconstruct (Sec. IV-E).  The lower edges of the chunk's bin range and of
+  // the bin above it go to a table in the spare buffer when the range is small
+  // enough, so that each distinct bin's edge is found once.
   using Key = typename Tr::Bin;  // order keys fit the signed bin type
+  using UKey = std::make_unsigned_t<Key>;
   constexpr uint32_t kTab = kChunkBytes / sizeof(Key);
-  constexpr Key kNoKey = (Key)((uint64_t)1 << (8 * sizeof(Key) - 1));  // most negative
-  for (int w = 0; w < kCW; ++w) {
-    bmin = min(bmin, s_mm[0][w]);
-    bmax = max(bmax, s_mm[1][w]);
-  }
-  // the table also holds the floor of bin bmax + 1: the keys of bin b are
-  // those from floor(b) up to floor(b + 1) (the bins are monotone in the
-  // value), so a point whose next bin has a floor needs no re-quantization
-  const bool table = (uint64_t)bmax - (uint64_t)bmin < kTab - 1;
-  Key* T = (Key*)spare;
-  if (table) {
-    const uint32_t R = (uint32_t)((uint64_t)bmax - (uint64_t)bmin) + 2;
-    for (uint32_t e = threadIdx.x; e < R; e += kCT) {
-      int64_t klo;
-      T[e] = bin_floor_key<K>(bmin + (int64_t)e, inv, winv, klo) ? (Key)klo : kNoKey;
-    }
-  }
-  __syncthreads();
-  bool bad = false;
+  uint32_t olo = 0xffffffffu, ohi = 0;
 #pragma unroll
-  for (int i = 0; i < GPW; ++i) {
-    const uint32_t j = (wave() + kCW * i) * 64 + lane();
-    if (j >= nc) continue;
-    const int64_t b = K == 4 ? (int64_t)(int32_t)(uint32_t)wv[i] : (int64_t)(uint64_t)wv[i];
-    const uint64_t s = (uint64_t)sv[i];
-    int64_t klo;
-    bool have;
-    Key next = kNoKey;  // floor of bin b + 1, when known
-    if (table) {
-      const uint32_t e = (uint32_t)((uint64_t)b - (uint64_t)bmin);
-      const Key t = T[e];
-      next = T[e + 1];
-      have = t != kNoKey;
-      klo = (int64_t)t;
-    } else {
-      have = bin_floor_key<K>(b, inv, winv, klo);
+  for (int w = 0; w < kCW; ++w) {
+    olo = min(olo, s_mm[0][w]);
+    ohi = max(ohi, s_mm[1][w]);
+  }
+  const Word first = (Word)s_first - (Word)(1u << 30) + (Word)olo;  // the chunk's lowest bin
+  auto bin_of = [](Word v) -> int64_t {
+    return K == 4 ? (int64_t)(int32_t)(uint32_t)v : (int64_t)(uint64_t)v;
+  };
+  const int64_t bmin = bin_of(first), bmax = bmin + (int64_t)(uint64_t)(ohi - olo);
+  const bool table = !s_far && ohi - olo < kTab - 1 && bmin >= -Tr::kBinLimit &&
+                     bmax <= Tr::kBinLimit;
+  Key* T = (Key*)spare;
+  if (table)
+    for (uint32_t e = threadIdx.x; e < ohi - olo + 2; e += kCT)
+      T[e] = lower_edge<K>(bmin + (int64_t)e, inv, winv);
+  __syncthreads();
+  bool bad = false, odd = !table;
+  typename Tr::Raw v[PER];
+  if (table) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const bool on = full || j0 + i < nc;
+      const uint32_t e = on ? (uint32_t)(wv[i] - first) : 0u;
+      const Key t = T[e], next = T[e + 1];
+      odd |= on && (t == kNoKey<K> || next == kNoKey<K>);
+      // inside bin b iff below the edge of bin b + 1
+      bad |= on && sv[i] >= (Word)((UKey)next - (UKey)t);
+      v[i] = Tr::unkey((int64_t)(Key)((UKey)t + (UKey)sv[i]));
     }
-    typename Tr::Raw v = 0;
-    // the room above klo can exceed the int64 range: unsigned difference
-    if (!have || s > (uint64_t)Tr::kMaxKey - (uint64_t)klo) {
-      bad = true;
-    } else {
-      v = Tr::unkey(klo + (int64_t)s);
-      if (next != kNoKey) {
-        // inside bin b iff below the floor of bin b + 1
-        if (s >= (uint64_t)((int64_t)next - klo)) bad = true;
-      } else if (s && Tr::q(Tr::to_double(v), inv) != b) {
-        bad = true;
-      }
+  }
+  if (__ballot(odd)) {  // no table, or an edge is missing
+    bad = false;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (!full && j0 + i >= nc) break;
+      const int64_t b = bin_of(wv[i]);
+      bad |= !point_ok<K>(b, (uint64_t)sv[i], lower_edge<K>(b, inv, winv),
+                          lower_edge<K>(b + 1, inv, winv), inv, v[i]);
     }
-    out[p0 + j] = v;
+  }
+  // the thread's points are consecutive: 16-byte stores where the field
+  // allows (it need only be aligned to its elements)
+  typename Tr::Raw* dst = out + p0 + j0;
+  if (full && ((uintptr_t)out & 15u) == 0) {
+#pragma unroll
+    for (int q = 0; q < PER * K / 16; ++q) ((uint4*)dst)[q] = ((const uint4*)v)[q];
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (j0 + i < nc) dst[i] = v[i];
   }
   if (bad) set_status(prm, ST_FORMAT);
 }
