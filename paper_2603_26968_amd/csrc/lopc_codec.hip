@@ -123,31 +123,20 @@ __device__ void level_encode(const uint8_t* cur, uint32_t n, uint8_t* nxt,
   __syncthreads();
 }
 
-// LDS position of BIT_K unit u (plane u / G, group u % G).  In a full chunk
-// (G = 64 or 32, a power of two) the groups of plane j are stored
-// XOR-permuted by j, so the 8K lanes that store the planes of one group (a
-// row stride of G units) reach distinct LDS banks instead of one; partial
-// chunks keep the plain order (mask 0).
-struct UnitSwizzle {
-  uint32_t shift, mask;
-  __device__ __forceinline__ uint32_t operator()(uint32_t u) const {
-    return u ^ ((u >> shift) & mask);
-  }
-};
-
 // RZE_W over the first `len` bytes of the unit array U (zero beyond len)
 // into out.  Units from `nua` on are known to be zero (bit planes above the
-// highest set bit) and are skipped.  Returns the output length; pt = 1 when
+// highest set bit) and are not read.  Returns the output length; pt = 1 when
 // the input is stored verbatim because the output would not be smaller.
-// U may be stored swizzled (sw); the output is in plain byte order.
 template <int W>
 __device__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
-                               uint8_t* out, Scratch& sc, int& pt,
-                               UnitSwizzle sw = UnitSwizzle{0, 0}) {
+                               uint8_t* out, Scratch& sc, int& pt) {
+  constexpr int kRPW = (int)(kMaxRounds / kCW);  // rounds per wave at most
   const uint32_t NU = (len + 7) / 8;
   const uint32_t items = len / W;
   const uint32_t rounds = (NU + 63) / 64;
-  const uint32_t ra = (min(nua, NU) + 63) / 64;  // rounds that may hold nonzero units
+  const uint32_t na = min(nua, NU);
+  const uint32_t ra = (na + 63) / 64;  // rounds that may hold nonzero units
+  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane(wave());
   if (ra < rounds) {
     // bitmap bytes of the zero rounds, and their counts
     const uint32_t nb0 = (items + 7) / 8;
@@ -155,29 +144,39 @@ __device__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
     if (threadIdx.x >= ra && threadIdx.x < rounds) sc.rpre[threadIdx.x] = 0;
     __syncthreads();
   }
-  for (uint32_t r = wave(); r < ra; r += kCW) {
+  // the wave's units, their item bits and the inclusive counts of the rounds
+  uint64_t v[kRPW];
+  uint32_t mi[kRPW], inc[kRPW];
+#pragma unroll
+  for (int k = 0; k < kRPW; ++k) {
+    const uint32_t r = w0 + kCW * k;
+    v[k] = 0;
+    mi[k] = inc[k] = 0;
+    if (r >= ra) continue;
     const uint32_t u = r * 64 + lane();
-    const uint64_t v = u < NU ? U[sw(u)] : 0ull;
-    uint32_t mi, ci;
+    v[k] = u < na ? U[u] : 0ull;
+    uint32_t ci;
     if (W == 1) {
-      mi = nonzero_bytes(v);
-      ci = __popc(mi);
-      if (u < NU) sc.lv0[u] = (uint8_t)mi;
+      mi[k] = nonzero_bytes(v[k]);
+      ci = __popc(mi[k]);
+      if (u < NU) sc.lv0[u] = (uint8_t)mi[k];
     } else if (W == 4) {
-      mi = ((uint32_t)v != 0u) | ((uint32_t)((v >> 32) != 0ull) << 1);
-      ci = __popc(mi);
+      mi[k] = ((uint32_t)v[k] != 0u) | ((uint32_t)((v[k] >> 32) != 0ull) << 1);
+      ci = __popc(mi[k]);
       // lanes 4q+1..4q+3 lie in the row of lane 4q: DPP row shifts left
-      uint32_t b = mi | (dpp_u32<0x101, 0xf, true>(mi) << 2) |
-                   (dpp_u32<0x102, 0xf, true>(mi) << 4) | (dpp_u32<0x103, 0xf, true>(mi) << 6);
+      uint32_t b = mi[k] | (dpp_u32<0x101, 0xf, true>(mi[k]) << 2) |
+                   (dpp_u32<0x102, 0xf, true>(mi[k]) << 4) |
+                   (dpp_u32<0x103, 0xf, true>(mi[k]) << 6);
       if ((lane() & 3) == 0 && u < NU) sc.lv0[u / 4] = (uint8_t)b;
     } else {
-      mi = v != 0ull;
-      ci = mi;
-      uint64_t m = __ballot(mi);
+      mi[k] = v[k] != 0ull;
+      ci = mi[k];
+      uint64_t m = __ballot(mi[k]);
       if (lane() == 0) *(uint64_t*)(sc.lv0 + r * 8) = m;
     }
-    const uint32_t inc = wave_incl_scan(ci);
-    if (lane() == 63) sc.rpre[r] = inc;
+    inc[k] = wave_incl_scan(ci);
+    if (lane() == 63) sc.rpre[r] = inc[k];
+    inc[k] -= ci;
   }
   __syncthreads();
   const uint32_t npay = round_prefix(sc, rounds);
@@ -189,7 +188,7 @@ __device__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
   for (int l = 0; l < top; ++l) out_len += sc.nkept[l];
   if (out_len >= len) {
     const uint8_t* ub = (const uint8_t*)U;
-    for (uint32_t i = threadIdx.x; i < len; i += kCT) out[i] = ub[8 * sw(i >> 3) + (i & 7)];
+    for (uint32_t i = threadIdx.x; i < len; i += kCT) out[i] = i < 8 * na ? ub[i] : (uint8_t)0;
     pt = 1;
     __syncthreads();
     return len;
@@ -206,30 +205,25 @@ __device__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
     for (uint32_t i = threadIdx.x; i < sc.nkept[l]; i += kCT) out[pos + i] = kb[i];
     pos += sc.nkept[l];
   }
-  for (uint32_t r = wave(); r < ra; r += kCW) {
-    const uint32_t u = r * 64 + lane();
-    const uint64_t v = u < NU ? U[sw(u)] : 0ull;
-    uint32_t ci;
-    if (W == 1) ci = __popc(nonzero_bytes(v));
-    else if (W == 4) ci = ((uint32_t)v != 0u) + ((v >> 32) != 0ull);
-    else ci = v != 0ull;
-    uint32_t d = pos + W * (sc.rpre[r] + wave_incl_scan(ci) - ci);
-    if (u >= NU) continue;
+#pragma unroll
+  for (int k = 0; k < kRPW; ++k) {
+    const uint32_t r = w0 + kCW * k;
+    if (r >= ra) break;
+    uint32_t d = pos + W * (sc.rpre[r] + inc[k]);
     if (W == 1) {
 #pragma unroll
       for (int b = 0; b < 8; ++b) {
-        uint8_t x = (uint8_t)(v >> (8 * b));
-        if (x) out[d++] = x;
+        if ((mi[k] >> b) & 1u) out[d++] = (uint8_t)(v[k] >> (8 * b));
       }
     } else if (W == 4) {
-      uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+      const uint32_t lo = (uint32_t)v[k], hi = (uint32_t)(v[k] >> 32);
       if (lo) {
         put_bytes(out + d, lo, 4);
         d += 4;
       }
       if (hi) put_bytes(out + d, hi, 4);
     } else {
-      if (v) put_bytes(out + d, v, 8);
+      if (v[k]) put_bytes(out + d, v[k], 8);
     }
   }
   __syncthreads();
@@ -501,21 +495,79 @@ __device__ __forceinline__ bool rze_decode(const uint8_t* in, uint32_t in_len, u
   return true;
 }
 
-// BIT_K of the chunk's words, given per wave in registers: wv[i] is word
-// 64*g + lane of group g = wave + kCW*i.  Planes >= np are zero.
-template <int K, int GPW>
-__device__ void bit_encode(const typename Traits<K>::Word (&wv)[GPW], uint32_t G,
-                           uint32_t np, uint64_t* U, UnitSwizzle sw) {
+// bits of the four 4 x 4 blocks' rows (bytes) and columns exchanged, twice per
+// byte: steps of an 8 x 8 bit transpose inside half a matrix
+__device__ __forceinline__ uint32_t transpose4(uint32_t x) {
+  uint32_t t = (x ^ (x >> 7)) & 0x00aa00aau;
+  x ^= t ^ (t << 7);
+  t = (x ^ (x >> 14)) & 0x0000ccccu;
+  return x ^ t ^ (t << 14);
+}
+
+// planes 8C .. 8C + 7 of the thread's PER consecutive words (lo, hi: their
+// halves) into the units at `planes`
+template <int K, int C, int PER>
+__device__ __forceinline__ void bytes_to_planes(const uint32_t (&lo)[PER],
+                                                const uint32_t (&hi)[PER], uint32_t G,
+                                                uint32_t np, uint8_t* planes) {
+  if (np <= 8 * C) return;  // uniform
+  const uint32_t(&w)[PER] = C < 4 ? lo : hi;
+  // byte C of four words: rows of half a bit matrix
+  constexpr uint32_t D = C & 3, kPair = D | (D + 4) << 8 | 0x0c0c0000u;
+  auto four = [&](int i) {
+    return __builtin_amdgcn_perm(w[i + 1], w[i], kPair) |
+           __builtin_amdgcn_perm(w[i + 3], w[i + 2], kPair) << 16;
+  };
+  uint8_t* p = planes + (size_t)(8 * C) * G * 8;
+  if constexpr (K == 4) {
+    const uint32_t x = transpose4(four(0)), y = transpose4(four(4));
+    // rows: planes, columns: the eight words
+    const uint32_t l = (x & 0x0f0f0f0fu) | ((y << 4) & 0xf0f0f0f0u);
+    const uint32_t h = ((x >> 4) & 0x0f0f0f0fu) | (y & 0xf0f0f0f0u);
+    p += threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < GPW; ++i) {
-    const uint32_t g = wave() + kCW * i;
-    if (g >= G) break;
-    uint64_t mine = 0;
-    for (uint32_t j = 0; j < np; ++j) {
-      uint64_t b = __ballot((wv[i] >> j) & 1);
-      if (lane() == (int)j) mine = b;
+    for (int j = 0; j < 4; ++j) {
+      p[j * (G * 8)] = (uint8_t)(l >> (8 * j));
+      p[(j + 4) * (G * 8)] = (uint8_t)(h >> (8 * j));
     }
-    if (lane() < 8 * K) U[sw(lane() * G + g)] = mine;
+  } else {
+    // the four words are half of each plane byte: a pair of threads joins its
+    // halves, the even one for planes 8C .. 8C + 3, the odd one for the others
+    const uint32_t x = transpose4(four(0));
+    const uint32_t y = dpp_u32<0xb1, 0xf, true>(x);  // the other thread of the pair
+    const bool odd = threadIdx.x & 1u;
+    const uint32_t a = odd ? y >> 4 : x, b = odd ? x : y << 4;
+    const uint32_t l = (a & 0x0f0f0f0fu) | (b & 0xf0f0f0f0u);
+    p += (odd ? 4 * (G * 8) : 0u) + (threadIdx.x >> 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j * (G * 8)] = (uint8_t)(l >> (8 * j));
+  }
+}
+// BIT_K of a chunk: thread t holds its PER consecutive words t * PER ..; planes
+// from np on are zero, and those from the next multiple of 8 on are not
+// written.  The inverse of planes_to_words: about 45 (25) vector instructions
+// for 8 x 8 (8 x 4) bits, where one ballot per plane and group took about 4
+// per plane for a word.
+template <int K, int PER>
+__device__ __forceinline__ void words_to_planes(const typename Traits<K>::Word (&w)[PER],
+                                                uint32_t G, uint32_t np, uint64_t* U) {
+  uint32_t lo[PER], hi[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    lo[i] = (uint32_t)w[i];
+    hi[i] = K == 8 ? (uint32_t)((uint64_t)w[i] >> 32) : 0u;
+  }
+  if (threadIdx.x >= (K == 4 ? G * 8 : G * 16)) return;
+  uint8_t* p = (uint8_t*)U;
+  bytes_to_planes<K, 0, PER>(lo, hi, G, np, p);
+  bytes_to_planes<K, 1, PER>(lo, hi, G, np, p);
+  bytes_to_planes<K, 2, PER>(lo, hi, G, np, p);
+  bytes_to_planes<K, 3, PER>(lo, hi, G, np, p);
+  if constexpr (K == 8) {
+    bytes_to_planes<K, 4, PER>(lo, hi, G, np, p);
+    bytes_to_planes<K, 5, PER>(lo, hi, G, np, p);
+    bytes_to_planes<K, 6, PER>(lo, hi, G, np, p);
+    bytes_to_planes<K, 7, PER>(lo, hi, G, np, p);
   }
 }
 
@@ -533,17 +585,6 @@ __device__ uint64_t nonzero_planes(const uint64_t* U, uint32_t G, Scratch& sc) {
   }
   __syncthreads();
   return sc.planes;
-}
-
-__device__ __forceinline__ uint64_t block_or(uint64_t v, Scratch& sc) {
-  // wave OR by ballots over the set bits is costly; reduce through LDS
-  v = wave_reduce(v, OpOr{});
-  if (lane() == 0) sc.orv[wave()] = v;
-  __syncthreads();
-  uint64_t r = 0;
-  for (int w = 0; w < kCW; ++w) r |= sc.orv[w];
-  __syncthreads();
-  return r;
 }
 
 constexpr uint64_t kLbAgg = 1ull << 62, kLbInc = 2ull << 62,
@@ -605,7 +646,7 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   using Tr = Traits<K>;
   using Word = typename Tr::Word;
   constexpr uint32_t W = kChunkBytes / K;
-  constexpr int GPW = (int)(W / 64 / kCW);  // groups per wave
+  constexpr int PER = (int)(W / kCT);  // consecutive words of a thread
   // LDS: the look-back path keeps the bins part (B) until the end beside
   // the RZE_K output (X): 54,248 bytes, three workgroups per CU.  The slot
   // path parks the bins part as soon as it is known and reuses B for X:
@@ -617,7 +658,7 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   __shared__ uint32_t s_btail;  // slot path: bytes of the bins part's partial last word
   __shared__ Scratch sc;
   // the record header and the chunk's offset live in sc.orv, which is free
-  // once both block_or calls are done
+  // once the planes in use are known
   uint8_t* hdr = (uint8_t*)sc.orv;
   uint64_t& s_excl = sc.orv[2];
 
@@ -628,70 +669,76 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   const uint32_t L = m * K;
   const Word M = (Word)0xAAAAAAAAAAAAAAAAull;
 
-  const UnitSwizzle sw{(uint32_t)__builtin_ctz(W / 64), G == W / 64 ? G - 1 : 0u};
-
-  // The chunk's bins and subbins come in as 16-byte vectors through LDS
-  // (U and B are free until the bit planes): four vector loads per thread
-  // instead of three word loads per value.
+  // The thread's bins and subbins, as 16-byte vectors (the rows of a chunk
+  // start on one).  bins: DIFFNB_K (delta from the previous bin, 0 before the
+  // chunk, then negabinary), zero words up to m.
+  Word wv[PER], sv[PER];
+  const uint32_t j0 = threadIdx.x * PER;
+  const bool full = nc == W;
   {
-    const uint4* bsrc = (const uint4*)(bins + p0);
-    const uint4* ssrc = (const uint4*)(sub + p0);
-    constexpr uint32_t VB = 16 / sizeof(typename Tr::Bin), VS = 4;  // values per vector
-    const uint32_t nb = nc / VB, ns = nc / VS;
-    uint4 vb[(W / VB + kCT - 1) / kCT], vs[(W / VS + kCT - 1) / kCT];
+    typename Tr::Bin bn[PER];
+    uint32_t sb[PER];
+    const typename Tr::Bin* bsrc = bins + p0 + j0;
+    const uint32_t* ssrc = sub + p0 + j0;
+    // the bin before the wave's first
+    typename Tr::Bin before = 0;
+    if (threadIdx.x >= 64 && lane() == 0 && j0 <= nc) before = bsrc[-1];
+    if (full) {
 #pragma unroll
-    for (int q = 0; q < (int)((W / VB + kCT - 1) / kCT); ++q) {
-      const uint32_t i = threadIdx.x + q * kCT;
-      vb[q] = i < nb ? bsrc[i] : make_uint4(0, 0, 0, 0);
-    }
+      for (int q = 0; q < PER * K / 16; ++q) ((uint4*)bn)[q] = ((const uint4*)bsrc)[q];
 #pragma unroll
-    for (int q = 0; q < (int)((W / VS + kCT - 1) / kCT); ++q) {
-      const uint32_t i = threadIdx.x + q * kCT;
-      vs[q] = i < ns ? ssrc[i] : make_uint4(0, 0, 0, 0);
-    }
+      for (int q = 0; q < PER / 4; ++q) ((uint4*)sb)[q] = ((const uint4*)ssrc)[q];
+    } else {
 #pragma unroll
-    for (int q = 0; q < (int)((W / VB + kCT - 1) / kCT); ++q) {
-      const uint32_t i = threadIdx.x + q * kCT;
-      if (i < nb) ((uint4*)U)[i] = vb[q];
+      for (int i = 0; i < PER; ++i) {
+        bn[i] = j0 + i < nc ? bsrc[i] : 0;
+        sb[i] = j0 + i < nc ? ssrc[i] : 0u;
+      }
     }
+    // from the lane below (wave_shr:1), its last bin; lane 0 keeps `before`
+    typename Tr::Bin prev;
+    const uint64_t lastb = (uint64_t)bn[PER - 1], bef = (uint64_t)before;
+    uint64_t pv = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)bef, (int)(uint32_t)lastb,
+                                                        0x138, 0xf, 0xf, false);
+    if constexpr (K == 8)
+      pv |= (uint64_t)(uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(bef >> 32),
+                                                            (int)(uint32_t)(lastb >> 32), 0x138,
+                                                            0xf, 0xf, false) << 32;
+    prev = (typename Tr::Bin)pv;
+    Word ob = 0, os = 0;
 #pragma unroll
-    for (int q = 0; q < (int)((W / VS + kCT - 1) / kCT); ++q) {
-      const uint32_t i = threadIdx.x + q * kCT;
-      if (i < ns) ((uint4*)B)[i] = vs[q];
+    for (int i = 0; i < PER; ++i) {
+      const Word d = (Word)bn[i] - (Word)prev;
+      prev = bn[i];
+      wv[i] = full || j0 + i < nc ? (d + M) ^ M : (Word)0;
+      sv[i] = (Word)sb[i];
+      ob |= wv[i];
+      os |= sv[i];
     }
-    // the ragged end of a last chunk, one value per thread
-    for (uint32_t j = nb * VB + threadIdx.x; j < nc; j += kCT)
-      ((typename Tr::Bin*)U)[j] = bins[p0 + j];
-    for (uint32_t j = ns * VS + threadIdx.x; j < nc; j += kCT) ((uint32_t*)B)[j] = sub[p0 + j];
+    // the highest planes in use
+    ob = wave_reduce(ob, OpOr{});
+    const uint32_t os32 = wave_reduce((uint32_t)os, OpOr{});
+    if (lane() == 0) {
+      sc.orv[wave()] = (uint64_t)ob;
+      sc.scan[wave()] = os32;
+    }
   }
   __syncthreads();
-
-  // bins: DIFFNB_K (delta from the previous bin, 0 before the chunk, then
-  // negabinary), zero words up to m, BIT_K, RZE_1
-  Word wv[GPW], sv[GPW];
-  uint64_t orv = 0;
+  uint64_t orb = 0;
+  uint32_t ors = 0;
 #pragma unroll
-  for (int i = 0; i < GPW; ++i) {
-    const uint32_t g = wave() + kCW * i;
-    const uint32_t j = g * 64 + lane();
-    Word v = 0;
-    if (j < nc) {
-      const typename Tr::Bin* lb = (const typename Tr::Bin*)U;
-      Word cur = (Word)lb[j];
-      Word prev = j ? (Word)lb[j - 1] : (Word)0;
-      Word d = cur - prev;
-      v = (d + M) ^ M;
-    }
-    sv[i] = j < nc ? (Word)((const uint32_t*)B)[j] : (Word)0;
-    wv[i] = v;
-    orv |= (uint64_t)v;
+  for (int w = 0; w < kCW; ++w) {
+    orb |= sc.orv[w];
+    ors |= sc.scan[w];
   }
-  orv = block_or(orv, sc);
-  uint32_t np = orv ? 64 - (uint32_t)__builtin_clzll(orv) : 0;
-  bit_encode<K, GPW>(wv, G, np, U, sw);
+  const uint32_t npb = (uint32_t)__builtin_amdgcn_readfirstlane(
+      orb ? 64 - __builtin_clzll(orb) : 0);
+  const uint32_t nps = (uint32_t)__builtin_amdgcn_readfirstlane(ors ? 32 - __builtin_clz(ors) : 0);
+  // BIT_K, RZE_1
+  words_to_planes<K, PER>(wv, G, npb, U);
   __syncthreads();
   int pt_b = 0, pt_s1 = 0, pt_s2 = 0;
-  const uint32_t blen = rze_encode<1>(U, L, np * G, (uint8_t*)B, sc, pt_b, sw);
+  const uint32_t blen = rze_encode<1>(U, L, npb * G, (uint8_t*)B, sc, pt_b);
   const bool last = c == nch - 1;
   const uint32_t room = last ? S.tail_len : S.len[0] + S.len[1] + S.len[2];
   if constexpr (kSlot) {
@@ -705,15 +752,10 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
     __syncthreads();  // B is free for the RZE_K output
   }
 
-  // subbins: zero words up to m, BIT_K, RZE_K, RZE_1
-  orv = 0;
-#pragma unroll
-  for (int i = 0; i < GPW; ++i) orv |= (uint64_t)sv[i];
-  orv = block_or(orv, sc);
-  np = orv ? 64 - (uint32_t)__builtin_clzll(orv) : 0;
-  bit_encode<K, GPW>(sv, G, np, U, sw);
+  // subbins: BIT_K, RZE_K, RZE_1
+  words_to_planes<K, PER>(sv, G, nps, U);
   __syncthreads();
-  const uint32_t smid = rze_encode<K>(U, L, np * G, (uint8_t*)X, sc, pt_s1, sw);
+  const uint32_t smid = rze_encode<K>(U, L, nps * G, (uint8_t*)X, sc, pt_s1);
   if (threadIdx.x < 16) ((uint8_t*)X)[smid + threadIdx.x] = 0;  // zero units past smid
   __syncthreads();
   const uint32_t slen = rze_encode<1>(X, smid, (smid + 7) / 8, (uint8_t*)U, sc, pt_s2);
@@ -1114,14 +1156,6 @@ __device__ __forceinline__ void put_byte(uint32_t& w, uint32_t t) {
   LOPC_PUT4(3);
 #undef LOPC_PUT4
 #undef LOPC_PUT
-}
-// bits of the four 4 x 4 blocks' rows (bytes) and columns exchanged, twice per
-// byte: steps of an 8 x 8 bit transpose inside half a matrix
-__device__ __forceinline__ uint32_t transpose4(uint32_t x) {
-  uint32_t t = (x ^ (x >> 7)) & 0x00aa00aau;
-  x ^= t ^ (t << 7);
-  t = (x ^ (x >> 14)) & 0x0000ccccu;
-  return x ^ t ^ (t << 14);
 }
 // bit b (0..3) of m as byte b of all ones
 __device__ __forceinline__ uint32_t byte_mask(uint32_t m) {
