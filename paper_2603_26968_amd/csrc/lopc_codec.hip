@@ -34,15 +34,12 @@ constexpr int kCW = kCT / 64;   // its waves
 constexpr uint32_t kMaxUnits = kChunkBytes / 8;  // 2048
 constexpr uint32_t kMaxRounds = kMaxUnits / 64;  // 32
 
-// Scratch of the unit-parallel RZE stages.
+// Scratch of the decoder's unit-parallel RZE stages.
 struct Scratch {
   uint8_t lv0[kMaxUnits + 16] __attribute__((aligned(16)));  // level-1 bitmap
   uint8_t lv1[256 + 16] __attribute__((aligned(16)));
   uint8_t lv2[32 + 16] __attribute__((aligned(16)));
   uint8_t lv3[16] __attribute__((aligned(16)));
-  uint8_t kp0[kMaxUnits];  // kept bytes of the level-1 bitmap
-  uint8_t kp1[256];
-  uint8_t kp2[32];
   uint32_t rpre[kMaxRounds + 1];  // per-round totals, then exclusive prefix
   uint32_t scan[kCW + 1];
   uint32_t nkept[4];
@@ -54,10 +51,6 @@ struct Scratch {
 __device__ __forceinline__ uint8_t* lvl(Scratch& sc, int l) {
   return l == 0 ? sc.lv0 : (l == 1 ? sc.lv1 : (l == 2 ? sc.lv2 : sc.lv3));
 }
-__device__ __forceinline__ uint8_t* kept(Scratch& sc, int l) {
-  return l == 0 ? sc.kp0 : (l == 1 ? sc.kp1 : sc.kp2);
-}
-
 // Bitmap bytes of RZE level l for `items` items: ceil(items / 8^(l+1)) (each
 // level is the bitmap of the one below; nested ceilings compose).  Computed
 // rather than tabulated so that nothing lands in a private array.
@@ -74,146 +67,181 @@ __device__ __forceinline__ int rze_top(uint32_t items) {
 
 // bit b (0..7) of the result: byte b of v is nonzero
 __device__ __forceinline__ uint32_t nonzero_bytes(uint64_t v) {
-  uint64_t t = v | (v >> 4);
-  t |= t >> 2;
-  t |= t >> 1;
-  t &= 0x0101010101010101ull;
-  return (uint32_t)((t * 0x0102040810204080ull) >> 56);
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  // 0x80 in the bytes that are not zero, then their places' sum
+  const uint32_t l = (((lo & 0x7f7f7f7fu) + 0x7f7f7f7fu) | lo) & 0x80808080u;
+  const uint32_t h = (((hi & 0x7f7f7f7fu) + 0x7f7f7f7fu) | hi) & 0x80808080u;
+  return __builtin_amdgcn_udot4(h, 0x80402010u, __builtin_amdgcn_udot4(l, 0x08040201u, 0u, false),
+                                false) >> 7;
 }
 
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t c) { return wave_scan_u32(c); }
 
-// Turn the per-round totals sc.rpre[0..rounds) into exclusive prefixes and
-// return the grand total.  Call between barriers.
-__device__ __forceinline__ uint32_t round_prefix(Scratch& sc, uint32_t rounds) {
-  if (threadIdx.x < 64) {
-    uint32_t c = threadIdx.x < rounds ? sc.rpre[threadIdx.x] : 0u;
-    uint32_t inc = wave_incl_scan(c);
-    if (threadIdx.x < rounds) sc.rpre[threadIdx.x] = inc - c;
-    if (threadIdx.x == 63) sc.rpre[kMaxRounds] = inc;
-  }
-  __syncthreads();
-  return sc.rpre[kMaxRounds];
-}
+// Scratch of rze_encode.
+struct EncScratch {
+  // the lowest bitmap level kept in memory (RZE_1: level 1, RZE_K: level 0)
+  // and the two above it
+  uint8_t lva[512 + 16] __attribute__((aligned(16)));
+  uint8_t lvb[64 + 16] __attribute__((aligned(16)));
+  uint8_t lvc[16] __attribute__((aligned(16)));
+  uint32_t rpre[kMaxRounds];  // per round: kept items, kept level-0 bytes << 16
+  uint32_t scan[kCW];
+  uint32_t pos0, out_len;     // offset of the kept level-0 bytes; the output's length
+  uint64_t orv[kCW];
+};
 
-// One level of the bitmap recursion: bit i of nxt = cur[i] differs from the
-// byte before it (0 before the first); the differing bytes go to kp.
-__device__ void level_encode(const uint8_t* cur, uint32_t n, uint8_t* nxt,
-                             uint8_t* kp, uint32_t& nk, Scratch& sc) {
-  const uint32_t nb = (n + 7) / 8;  // <= 256
-  uint32_t bits = 0;
-  if (threadIdx.x < nb) {
-    uint32_t i0 = threadIdx.x * 8;
-    uint8_t prev = i0 ? cur[i0 - 1] : (uint8_t)0;
-    for (uint32_t b = 0; b < 8 && i0 + b < n; ++b) {
-      uint8_t v = cur[i0 + b];
-      bits |= (uint32_t)(v != prev) << b;
-      prev = v;
-    }
-    nxt[threadIdx.x] = (uint8_t)bits;
+// One level of the bitmap recursion by one wave, for levels of at most 512
+// bytes: lane l takes bytes 8l .. of cur[0, n), bit b of `bits`: its byte b
+// differs from the byte before it (0 before the first).  The bits are the
+// next level's byte l.
+struct LevelStep {
+  uint64_t v;
+  uint32_t bits, excl, total;
+  __device__ __forceinline__ void run(const uint8_t* cur, uint32_t n, uint8_t* nxt) {
+    const uint32_t i0 = (uint32_t)lane() * 8;
+    v = i0 < n ? ((const uint64_t*)cur)[lane()] : 0ull;
+    const uint32_t prev = dpp_u32<0x138, 0xf, true>((uint32_t)(v >> 56));  // the lane below
+    bits = nonzero_bytes(v ^ (v << 8 | prev));
+    const uint32_t valid = i0 < n ? n - i0 : 0u;
+    if (valid < 8) bits &= (1u << valid) - 1u;
+    if (i0 < n) nxt[lane()] = (uint8_t)bits;
+    const uint32_t c = (uint32_t)__popc(bits);
+    excl = wave_incl_scan(c);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)excl, 63);
+    excl -= c;
+    __builtin_amdgcn_wave_barrier();
   }
-  uint32_t tot;
-  uint32_t e = block_excl_scan<uint32_t, kCW>((uint32_t)__popc(bits), sc.scan, tot);
-  if (threadIdx.x < nb) {
-    uint32_t i0 = threadIdx.x * 8;
-    for (uint32_t b = 0; b < 8; ++b)
-      if ((bits >> b) & 1) kp[e++] = cur[i0 + b];
+  __device__ __forceinline__ void put(uint8_t* out) const {
+    uint8_t* p = out + excl;
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+      if ((bits >> b) & 1u) *p++ = (uint8_t)(v >> (8 * b));
   }
-  nk = tot;
-  __syncthreads();
-}
+};
 
-// RZE_W over the first `len` bytes of the unit array U (zero beyond len)
-// into out.  Units from `nua` on are known to be zero (bit planes above the
-// highest set bit) and are not read.  Returns the output length; pt = 1 when
-// the input is stored verbatim because the output would not be smaller.
+// RZE_W over the first `len` bytes of the unit array U into out (whole units:
+// up to 7 bytes past the output's length are written).  Units from `nua` on
+// are known to be zero (bit planes above the highest set bit) and are not
+// read.  Returns the output length; pt = 1 when the input is stored verbatim
+// because the output would not be smaller.
+//
+// What bounds it is the chain of barriers, not the work between them: with a
+// pass and a block-wide scan for every bitmap level a chunk's three RZE
+// stages took about 45, and k_encode of a 1800x3600 binary32 field ran at 31%
+// of the vector issue rate.  Three are left.  Each wave takes a run of the rounds of
+// 64 units that may hold something, keeps its units in registers, and one
+// ballot gives the round's 64 bits of level 1; a round's counts of kept items
+// and kept level-0 bytes go out packed in one word.  Then every wave sums the
+// rounds' counts for itself while the first one forms the levels above (at
+// most 512 bytes, one lane per 8), and after the next barrier all write.
 template <int W>
-__device__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
-                               uint8_t* out, Scratch& sc, int& pt) {
-  constexpr int kRPW = (int)(kMaxRounds / kCW);  // rounds per wave at most
+__device__ __forceinline__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
+                                               uint8_t* out, EncScratch& sc, int& pt) {
+  constexpr uint32_t kRPW = kMaxRounds / kCW;       // rounds per wave at most
+  constexpr uint32_t kLB = W == 1 ? 8 : 64 / W;     // bytes of lva per round
   const uint32_t NU = (len + 7) / 8;
   const uint32_t items = len / W;
   const uint32_t rounds = (NU + 63) / 64;
   const uint32_t na = min(nua, NU);
   const uint32_t ra = (na + 63) / 64;  // rounds that may hold nonzero units
-  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane(wave());
-  if (ra < rounds) {
-    // bitmap bytes of the zero rounds, and their counts
-    const uint32_t nb0 = (items + 7) / 8;
-    for (uint32_t i = threadIdx.x; i < (nb0 + 3) / 4 + 1; i += kCT) ((uint32_t*)sc.lv0)[i] = 0;
-    if (threadIdx.x >= ra && threadIdx.x < rounds) sc.rpre[threadIdx.x] = 0;
-    __syncthreads();
-  }
-  // the wave's units, their item bits and the inclusive counts of the rounds
-  uint64_t v[kRPW];
-  uint32_t mi[kRPW], inc[kRPW];
+  // the first round without any may still differ from the byte before it
+  const uint32_t rz = W == 1 ? min(rounds, ra + 1) : ra;
+  const uint32_t rpw = (rz + kCW - 1) / kCW;
+  const int top = rze_top(items);
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane(wave()) * rpw;
+  if (threadIdx.x < kMaxRounds * kLB / 4 && threadIdx.x >= rz * kLB / 4)
+    ((uint32_t*)sc.lva)[threadIdx.x] = 0;  // the zero rounds
+  uint64_t v[kRPW], dm[kRPW];
+  uint32_t mi[kRPW], ex[kRPW];
+  uint32_t prev = 0;  // the level-0 byte before the round
+  if (W == 1 && r0 > 0 && r0 * 64 - 1 < na) prev = nonzero_bytes(U[r0 * 64 - 1]);
 #pragma unroll
-  for (int k = 0; k < kRPW; ++k) {
-    const uint32_t r = w0 + kCW * k;
-    v[k] = 0;
-    mi[k] = inc[k] = 0;
-    if (r >= ra) continue;
+  for (uint32_t k = 0; k < kRPW; ++k) {
+    const uint32_t r = r0 + k;
+    v[k] = dm[k] = 0;
+    mi[k] = ex[k] = 0;
+    if (k >= rpw || r >= rz) continue;
     const uint32_t u = r * 64 + lane();
     v[k] = u < na ? U[u] : 0ull;
-    uint32_t ci;
+    uint32_t c, kept0 = 0;
     if (W == 1) {
+      if ((len & 7u) && u == NU - 1) v[k] &= (1ull << (8 * (len & 7u))) - 1ull;
       mi[k] = nonzero_bytes(v[k]);
-      ci = __popc(mi[k]);
-      if (u < NU) sc.lv0[u] = (uint8_t)mi[k];
+      c = __popc(mi[k]);
+      if (top > 0) {
+        const uint32_t p = (uint32_t)__builtin_amdgcn_update_dpp((int)prev, (int)mi[k], 0x138, 0xf,
+                                                                 0xf, false);
+        prev = (uint32_t)__builtin_amdgcn_readlane((int)mi[k], 63);
+        dm[k] = __ballot(u < NU && mi[k] != p);
+        kept0 = (uint32_t)__popcll(dm[k]);
+        if (lane() == 0) ((uint64_t*)sc.lva)[r] = dm[k];
+      } else if (u < NU) {
+        sc.lva[u] = (uint8_t)mi[k];
+      }
     } else if (W == 4) {
       mi[k] = ((uint32_t)v[k] != 0u) | ((uint32_t)((v[k] >> 32) != 0ull) << 1);
-      ci = __popc(mi[k]);
+      c = __popc(mi[k]);
       // lanes 4q+1..4q+3 lie in the row of lane 4q: DPP row shifts left
-      uint32_t b = mi[k] | (dpp_u32<0x101, 0xf, true>(mi[k]) << 2) |
-                   (dpp_u32<0x102, 0xf, true>(mi[k]) << 4) |
-                   (dpp_u32<0x103, 0xf, true>(mi[k]) << 6);
-      if ((lane() & 3) == 0 && u < NU) sc.lv0[u / 4] = (uint8_t)b;
+      const uint32_t b = mi[k] | (dpp_u32<0x101, 0xf, true>(mi[k]) << 2) |
+                         (dpp_u32<0x102, 0xf, true>(mi[k]) << 4) |
+                         (dpp_u32<0x103, 0xf, true>(mi[k]) << 6);
+      if ((lane() & 3) == 0) sc.lva[u / 4] = (uint8_t)b;
     } else {
-      mi[k] = v[k] != 0ull;
-      ci = mi[k];
-      uint64_t m = __ballot(mi[k]);
-      if (lane() == 0) *(uint64_t*)(sc.lv0 + r * 8) = m;
+      mi[k] = c = v[k] != 0ull;
+      const uint64_t m = __ballot(mi[k]);
+      if (lane() == 0) ((uint64_t*)sc.lva)[r] = m;
     }
-    inc[k] = wave_incl_scan(ci);
-    if (lane() == 63) sc.rpre[r] = inc[k];
-    inc[k] -= ci;
+    ex[k] = wave_incl_scan(c);
+    if (lane() == 63) sc.rpre[r] = ex[k] | kept0 << 16;
+    ex[k] -= c;
   }
   __syncthreads();
-  const uint32_t npay = round_prefix(sc, rounds);
-  const int top = rze_top(items);
+  const uint32_t cr = (uint32_t)lane() < rz ? sc.rpre[lane()] : 0u;
+  const uint32_t ci = wave_incl_scan(cr);  // both counts fit 16 bits
+  const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)ci, 63);
+  const uint32_t before = ci - cr;
+  const uint32_t kept0 = all >> 16;
+  constexpr int kBase = W == 1 ? 1 : 0;  // the level in lva
+  const int steps = top - kBase;         // at most 2
+  LevelStep s0 = {}, s1 = {};
   const uint32_t sz_top = lvl_size(items, top);
-  for (int l = 0; l < top; ++l)
-    level_encode(lvl(sc, l), lvl_size(items, l), lvl(sc, l + 1), kept(sc, l), sc.nkept[l], sc);
-  uint32_t out_len = sz_top + npay * W;
-  for (int l = 0; l < top; ++l) out_len += sc.nkept[l];
+  if (r0 == 0 && threadIdx.x < 64) {
+    if (steps > 0) s0.run(sc.lva, lvl_size(items, kBase), sc.lvb);
+    if (steps > 1) s1.run(sc.lvb, lvl_size(items, kBase + 1), sc.lvc);
+    if (lane() == 0) {
+      sc.pos0 = sz_top + s1.total + s0.total;
+      sc.out_len = sc.pos0 + kept0 + (all & 0xffffu) * W;
+    }
+  }
+  __syncthreads();
+  const uint32_t out_len = (uint32_t)__builtin_amdgcn_readfirstlane((int)sc.out_len);
   if (out_len >= len) {
-    const uint8_t* ub = (const uint8_t*)U;
-    for (uint32_t i = threadIdx.x; i < len; i += kCT) out[i] = i < 8 * na ? ub[i] : (uint8_t)0;
+    for (uint32_t i = threadIdx.x; i < NU; i += kCT) ((uint64_t*)out)[i] = i < na ? U[i] : 0ull;
     pt = 1;
     __syncthreads();
     return len;
   }
   pt = 0;
-  uint32_t pos = 0;
-  {
-    const uint8_t* tb = lvl(sc, top);
-    for (uint32_t i = threadIdx.x; i < sz_top; i += kCT) out[i] = tb[i];
-    pos = sz_top;
-  }
-  for (int l = top - 1; l >= 0; --l) {
-    const uint8_t* kb = kept(sc, l);
-    for (uint32_t i = threadIdx.x; i < sc.nkept[l]; i += kCT) out[pos + i] = kb[i];
-    pos += sc.nkept[l];
+  const uint32_t pos0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sc.pos0);
+  if (threadIdx.x < 64) {
+    const uint8_t* tb = steps > 1 ? sc.lvc : (steps > 0 ? sc.lvb : sc.lva);
+    if ((uint32_t)lane() < sz_top) out[lane()] = tb[lane()];
+    if (steps > 1) s1.put(out + sz_top);
+    if (steps > 0) s0.put(out + sz_top + s1.total);
   }
 #pragma unroll
-  for (int k = 0; k < kRPW; ++k) {
-    const uint32_t r = w0 + kCW * k;
-    if (r >= ra) break;
-    uint32_t d = pos + W * (sc.rpre[r] + inc[k]);
+  for (uint32_t k = 0; k < kRPW; ++k) {
+    const uint32_t r = r0 + k;
+    if (k >= rpw || r >= rz) break;
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)before, (int)r);
+    uint32_t d = pos0 + kept0 + W * ((b & 0xffffu) + ex[k]);
     if (W == 1) {
+      const uint32_t lt = __builtin_amdgcn_mbcnt_hi((uint32_t)(dm[k] >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)dm[k], 0u));
+      if ((dm[k] >> lane()) & 1ull) out[pos0 + (b >> 16) + lt] = (uint8_t)mi[k];
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        if ((mi[k] >> b) & 1u) out[d++] = (uint8_t)(v[k] >> (8 * b));
+      for (int i = 0; i < 8; ++i) {
+        if ((mi[k] >> i) & 1u) out[d++] = (uint8_t)(v[k] >> (8 * i));
       }
     } else if (W == 4) {
       const uint32_t lo = (uint32_t)v[k], hi = (uint32_t)(v[k] >> 32);
@@ -653,10 +681,10 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   // about 37.9 KB, four workgroups per CU.
   __shared__ uint64_t U[kMaxUnits];      // bit planes; later the subbin part
   __shared__ uint64_t B[kMaxUnits + 2];  // bins part (slot path: then X)
-  __shared__ uint64_t Xb[kSlot ? 1 : kMaxUnits + 2];  // subbins after RZE_K (+16 zero bytes)
+  __shared__ uint64_t Xb[kSlot ? 1 : kMaxUnits + 2];  // subbins after RZE_K
   uint64_t* X = kSlot ? B : Xb;
   __shared__ uint32_t s_btail;  // slot path: bytes of the bins part's partial last word
-  __shared__ Scratch sc;
+  __shared__ EncScratch sc;
   // the record header and the chunk's offset live in sc.orv, which is free
   // once the planes in use are known
   uint8_t* hdr = (uint8_t*)sc.orv;
@@ -756,8 +784,6 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   words_to_planes<K, PER>(sv, G, nps, U);
   __syncthreads();
   const uint32_t smid = rze_encode<K>(U, L, nps * G, (uint8_t*)X, sc, pt_s1);
-  if (threadIdx.x < 16) ((uint8_t*)X)[smid + threadIdx.x] = 0;  // zero units past smid
-  __syncthreads();
   const uint32_t slen = rze_encode<1>(X, smid, (smid + 7) / 8, (uint8_t*)U, sc, pt_s2);
 
   const uint32_t size = record_size(blen, slen);
