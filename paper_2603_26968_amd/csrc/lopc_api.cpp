@@ -183,11 +183,12 @@ static int repair_by_sweeps(lopc_ctx* ctx, const Shape& s, const CompressLayout&
   uint64_t sweeps = 1, active = tl.ntiles;
   const uint32_t K = (uint32_t)ctx->sweep_hint;
   const size_t report = L.queue + sizeof(RepairQueue);
+  // few tiles are marked in the later half of the sweeps
   for (uint32_t t = 1; t <= K; ++t) {
     Ev e = t == 1 ? ev_first(ctx, LOPC_PHASE_REPAIR) : Ev{};
     if (t == K) e.b = ev_last(ctx, LOPC_PHASE_REPAIR).b;
     HIP_CTX(ctx, launch_repair(s.box, tl, (const uint16_t*)(ws + L.mask), sub, stamp,
-                               counters, t, hs, e));
+                               counters, t, 2 * t > K + 1, hs, e));
   }
   HIP_CTX(ctx, launch_encode(dtype, (uint32_t)s.n, ws + L.bins, sub, (uint16_t*)(ws + L.mask),
                              ws + L.tail, offs, (uint32_t*)(ws + L.parts), prm,
@@ -236,9 +237,10 @@ static int repair_by_sweeps(lopc_ctx* ctx, const Shape& s, const CompressLayout&
       return cap >= s.n + 2 ? LOPC_E_INTERNAL : kRestartOnQueue;  // the former unreachable
     }
     batch = (uint32_t)std::min<uint64_t>(batch, cap + 1 - next);  // the last group ends at cap
+    const bool few = (uint64_t)hc[1 + (next & 63)] * 8 < tl.ntiles;
     for (uint32_t b = 0; b < batch; ++b)
       HIP_CTX(ctx, launch_repair(s.box, tl, (const uint16_t*)(ws + L.mask), sub, stamp,
-                                 counters, next + b, hs,
+                                 counters, next + b, few, hs,
                                  b + 1 == batch ? ev_last(ctx, LOPC_PHASE_REPAIR) : Ev{}));
     HIP_CTX(ctx, hipMemcpyAsync(ctx->h_prm, ws, report, hipMemcpyDeviceToHost, hs));
     HIP_CTX(ctx, hipStreamSynchronize(hs));

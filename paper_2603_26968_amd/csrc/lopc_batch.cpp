@@ -218,10 +218,16 @@ uint32_t items(const BatchDesc& D, int ph, int g0, int g1) {
   return D.item0[ph][g1] - D.item0[ph][g0];
 }
 
+// Workgroups of a direct sweep: as many as stay resident.
+uint32_t sweep_grid(lopc_ctx* c, const BatchDesc& D) {
+  return std::min<uint32_t>((uint32_t)D.tiles, (uint32_t)(kRepairWaves * c->num_cu));
+}
+
 // The launch sequence of a batch, everything addressed from the workspace.
 // Persistent mode (persist_pct > 0): fixed grids drain the queues, so the
 // sequence does not depend on the batch's sizes.  Direct mode: one
-// workgroup per item, grids from the plan D.
+// workgroup per item (the sweeps: as many as stay resident), grids from the
+// plan D.
 hipError_t enqueue(lopc_ctx* c, int op, uint8_t* ws, const BatchDesc& D, uint32_t gmask,
                    int sweeps, hipStream_t s) {
   const BatchDesc* bd = (const BatchDesc*)ws;
@@ -255,7 +261,7 @@ hipError_t enqueue(lopc_ctx* c, int op, uint8_t* ws, const BatchDesc& D, uint32_
       if (pers)
         Q(launch_repair_p(c->tile2, c->tile3, bd, jobs, (uint32_t)t, grid_of(c, PK_REPAIR), s));
       else
-        Q(launch_repair_d(c->tile2, c->tile3, bd, jobs, (uint32_t)t, D.tiles, s));
+        Q(launch_repair_d(c->tile2, c->tile3, bd, jobs, (uint32_t)t, sweep_grid(c, D), s));
     }
     for (int d = 0; d < 2; ++d) {
       if (!has[d]) continue;
@@ -473,8 +479,8 @@ int lopc_compress_batch(lopc_ctx* ctx, int n, const lopc_job* jobs, void* d_ws,
           HIP_CTX(ctx, launch_repair_p(ctx->tile2, ctx->tile3, bd, dj, next + b,
                                        grid_of(ctx, PK_REPAIR), hs));
         else
-          HIP_CTX(ctx, launch_repair_d(ctx->tile2, ctx->tile3, bd, dj, next + b, P.desc.tiles,
-                                       hs));
+          HIP_CTX(ctx, launch_repair_d(ctx->tile2, ctx->tile3, bd, dj, next + b,
+                                       sweep_grid(ctx, P.desc), hs));
       }
       if (int st = read_back(ctx, P, ws, n, hs)) return st;
       hc = host_counters(ctx);

@@ -296,13 +296,17 @@ hipError_t launch_report(const Params* prm, const RepairQueue* q, uint64_t* d_si
 // saves.
 constexpr uint32_t kColourMinTiles = 32768;
 
+// Waves per SIMD, and so workgroups (of four waves) per CU, of a batch sweep.
+constexpr int kRepairWaves = 5;
+
 // One host-driven sweep: the tiles marked for `sweep`; with t.coloured,
 // in two launches by tile colour (checkerboard), so that a tile of the
 // second colour sees the changes of its face and corner neighbours in the
-// same sweep.  Ev: start of the first launch, end of the last.
+// same sweep.  few: expect few marked tiles (only how they are handed out
+// depends on it).  Ev: start of the first launch, end of the last.
 hipError_t launch_repair(Box box, Tiling t, const uint16_t* mask,
                          uint32_t* sub, uint32_t* stamp, uint32_t* counters,
-                         uint32_t sweep, hipStream_t s, Ev ev = {});
+                         uint32_t sweep, bool few, hipStream_t s, Ev ev = {});
 // Point worklists (LOPC_REPAIR_POINTS): list every point with flags for
 // iteration 0 (its length in ring[0]); one iteration `it` over the list win
 // (length ring[it % 64]) appending to wout (length ring[(it + 1) % 64]).
@@ -362,7 +366,7 @@ hipError_t launch_params_d(int dtype, const BatchDesc* bd, const Job* jobs, uint
 hipError_t launch_tile0_d(int group, int t2, int t3, const BatchDesc* bd, const Job* jobs,
                           uint32_t items, hipStream_t s);
 hipError_t launch_repair_d(int t2, int t3, const BatchDesc* bd, const Job* jobs, uint32_t sweep,
-                           uint32_t tiles, hipStream_t s);
+                           uint32_t grid, hipStream_t s);
 hipError_t launch_encode_d(int dtype, const BatchDesc* bd, const Job* jobs, int gate_sweep,
                            uint32_t items, hipStream_t s);
 hipError_t launch_decode_d(int dtype, const BatchDesc* bd, const Job* jobs, uint32_t items,

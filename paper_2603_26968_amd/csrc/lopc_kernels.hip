@@ -430,6 +430,9 @@ template <int NPT>
 constexpr uint32_t kEventShare = NPT / 16;
 // Events of a round up to which each gets a lane per neighbour.
 constexpr uint32_t kNarrow = 32;
+// Workgroups of a single-field sweep that expects few marked tiles: the six of
+// each of 256 CUs that k_repair_few's registers leave room for.
+constexpr uint32_t kFewGrid = 1536;
 
 // Event lists of a tile run (LDS indices of raised points; two alternating
 // lists per wave) and its block-wide words.
@@ -1175,11 +1178,11 @@ struct FacePoint {
   int64_t g;
   bool in;
 };
-__device__ __forceinline__ FacePoint face_point(const FaceSlot& f, const TileCoord& c,
+__device__ __forceinline__ FacePoint face_point(const FaceSlot& f, int ln, const TileCoord& c,
                                                 const Box& box, int64_t g00) {
   // (a plane has fewer than 2^32 points, so steps are 32-bit factors)
   const uint32_t nx = (uint32_t)box.nx, nyx = (uint32_t)box.ny * (uint32_t)box.nx;
-  const uint32_t r = (uint32_t)f.r0 + (uint32_t)lane();
+  const uint32_t r = (uint32_t)f.r0 + (uint32_t)ln;
   const uint32_t u = __umul24(r, (uint32_t)f.magic) >> 16, v = r - __umul24(u, (uint32_t)f.width);
   const bool uz = f.ua == 2, vy = f.va == 1;
   const uint32_t lz = (uint32_t)box.nz, ly = (uint32_t)box.ny;
@@ -1189,9 +1192,9 @@ __device__ __forceinline__ FacePoint face_point(const FaceSlot& f, const TileCoo
   const uint32_t lu = uz ? lz : ly, lv = vy ? ly : nx, bu = uz ? bz : by, bv = vy ? by : bx;
   // the axis the face is normal to (neither u's nor v's): in the grid for all
   // of it or none
-  const uint32_t pn = vy ? bx : uz ? by : bz, ln = vy ? nx : uz ? ly : lz;
+  const uint32_t pn = vy ? bx : uz ? by : bz, pl = vy ? nx : uz ? ly : lz;
   // lanes of the slot past the face, or none where the face is outside
-  const uint32_t lim = pn < ln ? (uint32_t)f.cnt : 0u;
+  const uint32_t lim = pn < pl ? (uint32_t)f.cnt : 0u;
   FacePoint p;
   p.in = (r < lim) & (bu + u < lu) & (bv + v < lv);
   const int64_t g0 = g00 + (int64_t)f.z * (int64_t)nyx + (int64_t)f.y * (int64_t)nx + f.x;
@@ -1324,7 +1327,7 @@ __device__ __forceinline__ uint32_t tile0_body(
     hu[q] = 0;
     hs[q] = 0;
     if (w + q * kWaves >= F::kSlots) continue;
-    const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], c, box, g00);
+    const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], lane(), c, box, g00);
     hu[q] = x[f.in ? f.g : g00];
     hin |= (uint32_t)f.in << q;
     hl[q] = f.li;
@@ -1517,6 +1520,7 @@ __attribute__((amdgpu_waves_per_eu(kTile0Waves<K, TZ, TY, TX>, 8))) void k_tile0
 // QM (queue mode): the tile was taken from the repair queue, and other
 // workgroups change subbins while it runs, so subbins are read and written
 // as relaxed atomics at agent scope (coherent across the XCDs' L2 caches).
+// LOOP: the tile is known to be marked, and the kernel runs several in turn.
 // With `blockers` given, thread 0 stores there the higher-index
 // neighbour tiles holding a same-bin lower neighbour of one of the tile's
 // points (the tiles its run depends on; bits 14..26 of the 27-direction set).
@@ -1528,7 +1532,7 @@ struct RunLds {
   EventLds<TZ * TY * TX> E;
   uint32_t go;
 };
-template <int TZ, int TY, int TX, bool QM = false>
+template <int TZ, int TY, int TX, bool QM = false, bool LOOP = false>
 __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
                             const uint16_t* __restrict__ mask, uint32_t* __restrict__ sub,
                             const uint32_t* stamp, uint32_t* counters,
@@ -1546,16 +1550,21 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
   // one read decides for the whole block (a neighbour may raise the stamp
   // concurrently)
   if (threadIdx.x == 0) {
-    lds.go = QM || stamp[t] >= sweep;
+    if (!LOOP) lds.go = QM || stamp[t] >= sweep;
     E.big = 0;
     E.over = 0;
     E.dirs = 0;
   }
   __syncthreads();
-  if (!lds.go) return 0;
+  if (!LOOP && !lds.go) return 0;
   c = tile_coord<TZ, TY, TX>(t, tl);
+  // in a loop: opaque, so that what follows from the thread's place alone is
+  // computed anew for each tile instead of held in registers across it
+  int tid = (int)threadIdx.x;
+  if (LOOP) asm volatile("" : "+v"(tid));
+  __builtin_assume(tid >= 0 && tid < kThreads);
   const int w = __builtin_amdgcn_readfirstlane(wave());
-  const int li0 = G::local(threadIdx.x);
+  const int li0 = G::local(tid);
   const int64_t nyx = (int64_t)box.ny * box.nx;
   const int64_t g00 = ((int64_t)c.z0 * box.ny + c.y0) * box.nx + c.x0;  // the tile's first point
   uint32_t ov[G::PER], hv[F::kPer];
@@ -1576,7 +1585,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
     };
 #pragma unroll
     for (int k = 0; k < G::PER; ++k) {
-      const int i = threadIdx.x + k * kThreads;
+      const int i = tid + k * kThreads;
       const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
       og[k] = g00 + iz * nyx + (int64_t)iy * box.nx + ix;
       take(og[k], c.z0 + iz < box.nz && c.y0 + iy < box.ny && c.x0 + ix < box.nx, ov[k], om[k]);
@@ -1587,7 +1596,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
       hv[q] = 0;
       hm[q] = 0;
       if (w + q * kWaves < F::kSlots) {
-        const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], c, box, g00);
+        const FacePoint f = face_point(kFaces<TZ, TY, TX>.s[w + q * kWaves], tid & 63, c, box, g00);
         take(f.g, f.in, hv[q], hm[q]);
         hl[q] = f.li;
       }
@@ -1603,7 +1612,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
       if (hl[q] >= 0) P[hl[q]] = (hv[q] | (uint32_t)hm[q] << 16) ^ (kNoFlags | kHalo);
       top = max(top, hv[q]);
     }
-    for (int i = threadIdx.x; i < Blind<TZ, TY, TX>::kCells; i += kThreads)
+    for (int i = tid; i < Blind<TZ, TY, TX>::kCells; i += kThreads)
       P[Blind<TZ, TY, TX>::cell(i)] = kNoFlags | kHalo;
     if (__ballot(top > kPackMax) && lane() == 0) E.big = 1;
     __syncthreads();
@@ -1628,7 +1637,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
     relax_wide<TZ, TY, TX>(P, om, counters, itot, t);
 #pragma unroll
     for (int k = 0; k < G::PER; ++k) {
-      const int i = threadIdx.x + k * kThreads;
+      const int i = tid + k * kThreads;
       const int li = G::local(i);
       const uint32_t v = P[li];
       if (QM && blockers && om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
@@ -1685,7 +1694,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
     for (int k = 0; k < G::PER; ++k) {
       const uint32_t wd = P[li0 + k * G::kSlot];
       if (QM && blockers) {
-        const int i = threadIdx.x + k * kThreads;
+        const int i = tid + k * kThreads;
         if (om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
       }
       if (wd & kRose) {
@@ -1758,6 +1767,53 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
   if (!dirs) return;
   if (colour < 2) mark_neighbours_col(dirs, c, tl, stamp, counters, sweep, colour);
   else mark_neighbours(dirs, c, tl, stamp, counters, sweep + 1);
+}
+
+// The same sweep where few tiles are marked: of the n tiles (of that colour) a
+// workgroup looks at every gridDim.x-th from its own on, all marks in one read,
+// and runs the marked ones in turn.  With a workgroup per tile a sweep takes the
+// time to start them all and read their marks: 30 us for 65,536 tiles of a
+// colour, whatever is marked.  Where most are marked that is the better: a
+// workgroup starts as another ends, and its registers leave room for eight
+// (512^3 float64, 24 launches: the later half this way 10.96 -> 10.63 ms a
+// call, all of them 12.35 ms).
+template <int TZ, int TY, int TX>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_repair_few(
+    Box box, Tiling tl, const uint16_t* __restrict__ mask,
+    uint32_t* __restrict__ sub, uint32_t* stamp, uint32_t* counters,
+    uint32_t sweep, uint32_t colour, uint32_t n) {
+  __shared__ RunLds<TZ, TY, TX> lds;
+  __shared__ uint64_t s_go;
+  const uint32_t b0 = xcd_tile(blockIdx.x, gridDim.x);
+  auto tile = [&](uint32_t b) { return colour < 2 ? colour_tile(b, colour, tl) : b; };
+  // one read decides for the whole block (a neighbour may raise the stamp
+  // concurrently); gridDim.x is at least n / 64
+  if (threadIdx.x < 64) {
+    const uint32_t b = b0 + (uint32_t)lane() * gridDim.x;
+    bool go = false;
+    if (b < n) {
+      const uint32_t t = tile(b);
+      go = t < tl.ntiles && stamp[t] >= sweep;
+    }
+    const uint64_t m = __ballot(go);
+    if (threadIdx.x == 0) s_go = m;
+  }
+  __syncthreads();
+  uint64_t go = s_go;
+  go = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)go) |
+       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(go >> 32)) << 32;
+  while (go) {
+    const uint32_t t = tile(b0 + (uint32_t)__builtin_ctzll(go) * gridDim.x);
+    go &= go - 1;
+    TileCoord c;
+    const uint32_t dirs = repair_body<TZ, TY, TX, false, true>(
+        lds, box, tl, mask, sub, stamp, counters, relax_total(counters), sweep, t, c);
+    if (dirs) {
+      if (colour < 2) mark_neighbours_col(dirs, c, tl, stamp, counters, sweep, colour);
+      else mark_neighbours(dirs, c, tl, stamp, counters, sweep + 1);
+    }
+    if (go) __syncthreads();  // the next tile's LDS
+  }
 }
 
 // Device-driven repair of a single field: a persistent grid takes tiles from
@@ -2048,7 +2104,7 @@ __global__ __launch_bounds__(kThreads) void k_tile0_p(const BatchDesc* bd, const
 }
 
 // One run of batch tile `t` of job J: the batch's 2D shape S2 or 3D shape S3.
-template <int S2, int S3>
+template <int S2, int S3, bool LOOP = false>
 __device__ __forceinline__ uint32_t batch_repair_run(const Job& J, uint32_t* err,
                                                      unsigned long long* itot, uint32_t sweep,
                                                      uint32_t t, TileCoord& c) {
@@ -2057,9 +2113,9 @@ __device__ __forceinline__ uint32_t batch_repair_run(const Job& J, uint32_t* err
   __shared__ __attribute__((aligned(16)))
   uint8_t lds[sizeof(L2) > sizeof(L3) ? sizeof(L2) : sizeof(L3)];
   if (J.tl.tz == 1)
-    return repair_body<1, kTile2[S2][1], kTile2[S2][2]>(*(L2*)lds, J.box, J.tl, J.mask, J.sub,
+    return repair_body<1, kTile2[S2][1], kTile2[S2][2], false, LOOP>(*(L2*)lds, J.box, J.tl, J.mask, J.sub,
                                                         J.stamp, err, itot, sweep, t, c);
-  return repair_body<kTile3[S3][0], kTile3[S3][1], kTile3[S3][2]>(
+  return repair_body<kTile3[S3][0], kTile3[S3][1], kTile3[S3][2], false, LOOP>(
       *(L3*)lds, J.box, J.tl, J.mask, J.sub, J.stamp, err, itot, sweep, t, c);
 }
 
@@ -2120,20 +2176,27 @@ __attribute__((amdgpu_waves_per_eu(kTile0Waves<K, TZ, TY, TX>, 8))) void k_tile0
   mark_list(dirs, c, J.tl, J.stamp, J.t0, bd->bc->lens, bd->lists + bd->tiles, 1);
 }
 
-// One sweep: workgroup b takes entry b of the sweep's work list (the grid
-// is the list's capacity; workgroups past its length exit at once).
+// One sweep: workgroup b takes the entries b, b + gridDim.x, ... of the sweep's
+// work list, with as many workgroups as stay resident (kRepairWaves per CU).
+// 48 fields, 25,550 tiles, 32 captured sweeps of which 13 find an empty list:
+// with a workgroup per tile such a sweep took 6.8 us to start and end them, and
+// the call 1,575 us; so 1,345 us (1,439 with a quarter more workgroups
+// than resident, 1,529 with half as many).
 template <int S2, int S3>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_repair_d(const BatchDesc* bd, const Job* jobs,
-                                                       uint32_t sweep) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kRepairWaves, 8))) void k_repair_d(
+    const BatchDesc* bd, const Job* jobs, uint32_t sweep) {
   BatchCounters* bc = bd->bc;
-  if (blockIdx.x >= bc->lens[sweep % kRing]) return;
-  const uint32_t item = bd->lists[(sweep & 1) * bd->tiles + blockIdx.x];
-  const Job& J = jobs[find_job<&Job::t0>(jobs, 0, (int)bd->job0[kGroups], item)];
+  const uint32_t n = bc->lens[sweep % kRing];
   uint32_t* list_out = bd->lists + ((sweep + 1) & 1) * bd->tiles;
-  TileCoord c;
-  const uint32_t dirs = batch_repair_run<S2, S3>(J, &bc->err, bc->relax_iters, sweep,
-                                                 item - J.t0, c);
-  if (dirs) mark_list(dirs, c, J.tl, J.stamp, J.t0, bc->lens, list_out, sweep + 1);
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const uint32_t item = bd->lists[(sweep & 1) * bd->tiles + i];
+    const Job& J = jobs[find_job<&Job::t0>(jobs, 0, (int)bd->job0[kGroups], item)];
+    TileCoord c;
+    const uint32_t dirs = batch_repair_run<S2, S3, true>(J, &bc->err, bc->relax_iters, sweep,
+                                                         item - J.t0, c);
+    if (dirs) mark_list(dirs, c, J.tl, J.stamp, J.t0, bc->lens, list_out, sweep + 1);
+    if (i + gridDim.x < n) __syncthreads();  // the next tile's LDS
+  }
 }
 
 }  // namespace
@@ -2257,15 +2320,22 @@ int repair_q_blocks_per_cu(int sid) {
 }
 
 hipError_t launch_repair(Box box, Tiling t, const uint16_t* mask, uint32_t* sub,
-                         uint32_t* stamp, uint32_t* counters, uint32_t sweep,
+                         uint32_t* stamp, uint32_t* counters, uint32_t sweep, bool few,
                          hipStream_t s, Ev ev) {
   // both colours, or every tile at once; the events bracket the sweep
   const bool col2 = t.coloured != 0;
   const uint32_t n =
       col2 ? (uint32_t)t.ntz * (uint32_t)t.nty * (uint32_t)((t.ntx + 1) / 2) : t.ntiles;
   const uint32_t nl = col2 ? 2 : 1;
+  // tiles a workgroup looks at where few are marked, and the workgroups then
+  const uint32_t per = few ? std::min(64u, (n + kFewGrid - 1) / kFewGrid) : 1u;
   for (uint32_t l = 0; l < nl; ++l) {
     Ev e{l == 0 ? ev.a : nullptr, l == nl - 1 ? ev.b : nullptr};
+    if (per > 1) {
+      LOPC_WITH_TILE(t, launch_ev(k_repair_few<TZ, TY, TX>, dim3((n + per - 1) / per), dim3(kThreads),
+                                  s, e, box, t, mask, sub, stamp, counters, sweep, col2 ? l : 2u, n));
+      continue;
+    }
     LOPC_WITH_TILE(t, launch_ev(k_repair<TZ, TY, TX>, dim3(n), dim3(kThreads), s, e, box, t,
                                 mask, sub, stamp, counters, sweep, col2 ? l : 2u));
   }
@@ -2378,9 +2448,9 @@ hipError_t launch_tile0_d(int group, int t2, int t3, const BatchDesc* bd, const 
 }
 
 hipError_t launch_repair_d(int t2, int t3, const BatchDesc* bd, const Job* jobs, uint32_t sweep,
-                           uint32_t tiles, hipStream_t s) {
-  if (!tiles) return hipSuccess;
-  LOPC_WITH_PAIR(t2, t3, (k_repair_d<S2, S3><<<tiles, kThreads, 0, s>>>(bd, jobs, sweep)));
+                           uint32_t grid, hipStream_t s) {
+  if (!grid) return hipSuccess;
+  LOPC_WITH_PAIR(t2, t3, (k_repair_d<S2, S3><<<grid, kThreads, 0, s>>>(bd, jobs, sweep)));
   return hipGetLastError();
 }
 

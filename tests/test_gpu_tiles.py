@@ -91,3 +91,13 @@ def test_float64_bins_far_from_the_first(P, ref, shape):
         # in the same bin in both orders, and equal low halves of the bins
         x = rng.choice(levels, shape) + rng.choice([-0.25, 0.0, 0.25], shape)
         check(P, ref, x.astype(np.float64), 1.0, f"bins {levels.tolist()}")
+
+
+def test_more_marked_tiles_than_resident_workgroups(P, ref):
+    # sweeps that hand several tiles to a workgroup: 3,780 tiles (2,100 of a
+    # colour) for at most 1,536 workgroups, few levels so that every sweep of
+    # several marks tiles all over the field
+    rng = np.random.default_rng(21)
+    z, y, x = np.meshgrid(np.arange(28), np.arange(477), np.arange(259), indexing="ij")
+    f = np.sin(z / 9.0) + np.sin(y / 23.0) * np.cos(x / 31.0) + rng.normal(0, 0.02, z.shape)
+    check(P, ref, f.astype(np.float32), 0.25, "many tiles")
