@@ -208,6 +208,11 @@ typedef struct {
   uint64_t relax_iterations;   /* in-tile relaxation passes, all tiles/sweeps */
 } lopc_batch_stats;
 
+/* dtype, ndim and dims of n decompress jobs from their 64-byte stream headers
+ * (h_headers: n of them in a row), checked as lopc_stream_info does; the other
+ * members stay.  The first bad header's status is returned. */
+int lopc_batch_read_headers(int n, const void* h_headers, lopc_job* jobs);
+
 /* Workspace bytes a batch of n jobs needs (op 0 = compress, 1 = decompress). */
 int lopc_batch_workspace_size(lopc_ctx* ctx, int op, int n, const lopc_job* jobs,
                               size_t* bytes);

@@ -419,6 +419,19 @@ int batch_common(lopc_ctx* c, int op, int n, const lopc_job* jobs, void* d_ws,
 
 extern "C" {
 
+int lopc_batch_read_headers(int n, const void* h_headers, lopc_job* jobs) {
+  if (n < 0 || (n && (!h_headers || !jobs))) return LOPC_E_ARG;
+  for (int i = 0; i < n; ++i) {
+    lopc_job& j = jobs[i];
+    int64_t d[3];
+    const int st = lopc_stream_info((const uint8_t*)h_headers + (size_t)i * kHeaderBytes,
+                                    kHeaderBytes, &j.dtype, &j.ndim, d, nullptr, nullptr);
+    if (st) return st;
+    for (int k = 0; k < j.ndim; ++k) j.dims[k] = d[k];
+  }
+  return LOPC_OK;
+}
+
 int lopc_batch_workspace_size(lopc_ctx* ctx, int op, int n, const lopc_job* jobs,
                               size_t* bytes) {
   if (!bytes || (op != 0 && op != 1)) return LOPC_E_ARG;

@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 import threading
 
 import torch
@@ -71,6 +72,11 @@ class Job(ctypes.Structure):
                 ("dims", ctypes.c_int64 * 3), ("error_bound", ctypes.c_double),
                 ("mode", ctypes.c_int), ("d_out_size", ctypes.c_void_p),
                 ("d_status", ctypes.c_void_p)]
+
+
+# the first four members of a Job; all but the two device addresses at its end
+_JOB_IO = struct.Struct("PNPN")
+_JOB = struct.Struct("PNPNii3qdi")
 
 
 class BatchStats(ctypes.Structure):
@@ -144,6 +150,7 @@ def load() -> ctypes.CDLL:
     jp = ctypes.POINTER(Job)
     L.lopc_batch_workspace_size.argtypes = [vp, ci, ci, jp, szp]
     L.lopc_batch_workspace_size.restype = ci
+    L.lopc_batch_read_headers.argtypes = [ci, vp, jp]
     L.lopc_compress_batch.argtypes = [vp, ci, jp, vp, sz, vp, ctypes.POINTER(BatchStats)]
     L.lopc_compress_batch.restype = ci
     L.lopc_decompress_batch.argtypes = [vp, ci, jp, vp, sz, vp]
@@ -566,12 +573,14 @@ def _compress_jobs(fields, error_bounds, modes, out, ctx):
         raise ValueError("one error bound and one mode per field")
     dev = fields[0].device
     ctx = context(dev.index) if ctx is None else ctx
-    caps = []
+    points = lopc_ctx_get_option(ctx, LOPC_OPT_REPAIR) == LOPC_REPAIR_POINTS
+    codes, caps = [], []
     for x in fields:
-        _check_field(x)
+        codes.append(_check_field(x))
         if x.device != dev:
             raise ValueError("all fields of a batch live on one device")
-        caps.append(_sizes_for(ctx, x.shape, x.dtype)[0])
+        v = _sizes.get((tuple(x.shape), x.dtype, points))
+        caps.append((v or _sizes_for(ctx, x.shape, x.dtype))[0])
     offs, total = [], 0
     for c in caps:
         offs.append(total)
@@ -579,18 +588,11 @@ def _compress_jobs(fields, error_bounds, modes, out, ctx):
     if out is None or out.numel() < total:
         out = torch.empty(total, dtype=torch.uint8, device=dev)
     jobs = (Job * n)()
-    base = out.data_ptr()
+    base, size = out.data_ptr(), ctypes.sizeof(Job)
     for i, x in enumerate(fields):
-        j = jobs[i]
-        j.d_in = x.data_ptr()
-        j.d_out = base + offs[i]
-        j.out_cap = caps[i]
-        j.dtype = _dtype_code(x.dtype)
-        j.ndim = x.dim()
-        for d in range(x.dim()):
-            j.dims[d] = int(x.shape[d])
-        j.error_bound = float(ebs[i])
-        j.mode = _mode(mds[i])
+        d = x.shape
+        _JOB.pack_into(jobs, i * size, x.data_ptr(), 0, base + offs[i], caps[i], codes[i], len(d),
+                       d[0], d[1], d[2] if len(d) == 3 else 0, float(ebs[i]), _mode(mds[i]))
     return jobs, out, offs, ctx, dev
 
 
@@ -651,22 +653,28 @@ def decompress_batch(streams, outs=None, workspace: torch.Tensor | None = None,
     if headers is None:
         heads = torch.stack([s[:HEADER_BYTES] for s in streams]).cpu().numpy()
         headers = [heads[i].tobytes() for i in range(n)]
-    infos = [lopc_stream_info(h) for h in headers]
+    # the shapes straight into the job table, one call for all headers (48
+    # separate ones and a store per member took most of the host's time)
+    heads = [bytes(h)[:HEADER_BYTES] for h in headers]
+    jobs = (Job * max(n, len(heads)))()
+    st = (LOPC_E_FORMAT if any(len(h) < HEADER_BYTES for h in heads) else
+          load().lopc_batch_read_headers(len(heads), b"".join(heads), jobs))
+    if st:
+        for h in heads:
+            lopc_stream_info(h)  # raises for the first bad one
+        raise LopcError(st, "lopc_stream_info")
     if outs is None:
-        outs = [torch.empty(inf["shape"], dtype=inf["dtype"], device=dev) for inf in infos]
-    jobs = (Job * n)()
-    for i, (s, inf, y) in enumerate(zip(streams, infos, outs)):
+        outs = [torch.empty(tuple(j.dims[:j.ndim]), device=dev,
+                            dtype=torch.float32 if j.dtype == LOPC_F32 else torch.float64)
+                for j in jobs[:len(heads)]]
+    at = 0
+    for s, _, y in zip(streams, heads, outs):
         if not s.is_cuda or s.dtype != torch.uint8 or not s.is_contiguous():
             raise ValueError("streams must be contiguous uint8 device tensors")
-        j = jobs[i]
-        j.d_in = s.data_ptr()
-        j.in_bytes = s.numel()
-        j.d_out = y.data_ptr()
-        j.out_cap = y.numel() * y.element_size()
-        j.dtype = _dtype_code(inf["dtype"])
-        j.ndim = len(inf["shape"])
-        for d, v in enumerate(inf["shape"]):
-            j.dims[d] = v
+        _JOB_IO.pack_into(jobs, at, s.data_ptr(), s.numel(), y.data_ptr(), y.nbytes)
+        at += ctypes.sizeof(Job)
+    if len(heads) != n:  # as many jobs as streams; one without a header is refused
+        jobs = (Job * n)(*jobs[:n])
     wsz = lopc_batch_workspace_size(ctx, 1, jobs)
     ws = _workspace(ctx, wsz, dev, workspace)
     st = lopc_decompress_batch(ctx, jobs, ws.data_ptr(), ws.numel(),
