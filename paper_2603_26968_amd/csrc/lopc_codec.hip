@@ -119,8 +119,8 @@ struct LevelStep {
   }
 };
 
-// RZE_W over the first `len` bytes of the unit array U into out (whole units:
-// up to 7 bytes past the output's length are written).  Units from `nua` on
+// RZE_W over the first `len` bytes of the unit array U, in place (the units
+// are in registers before the first byte is written).  Units from `nua` on
 // are known to be zero (bit planes above the highest set bit) and are not
 // read.  Returns the output length; pt = 1 when the input is stored verbatim
 // because the output would not be smaller.
@@ -135,8 +135,9 @@ struct LevelStep {
 // rounds' counts for itself while the first one forms the levels above (at
 // most 512 bytes, one lane per 8), and after the next barrier all write.
 template <int W>
-__device__ __forceinline__ uint32_t rze_encode(const uint64_t* U, uint32_t len, uint32_t nua,
-                                               uint8_t* out, EncScratch& sc, int& pt) {
+__device__ __forceinline__ uint32_t rze_encode(uint64_t* U, uint32_t len, uint32_t nua,
+                                               EncScratch& sc, int& pt) {
+  uint8_t* out = (uint8_t*)U;
   constexpr uint32_t kRPW = kMaxRounds / kCW;       // rounds per wave at most
   constexpr uint32_t kLB = W == 1 ? 8 : 64 / W;     // bytes of lva per round
   const uint32_t NU = (len + 7) / 8;
@@ -216,7 +217,7 @@ __device__ __forceinline__ uint32_t rze_encode(const uint64_t* U, uint32_t len, 
   __syncthreads();
   const uint32_t out_len = (uint32_t)__builtin_amdgcn_readfirstlane((int)sc.out_len);
   if (out_len >= len) {
-    for (uint32_t i = threadIdx.x; i < NU; i += kCT) ((uint64_t*)out)[i] = i < na ? U[i] : 0ull;
+    for (uint32_t i = na + threadIdx.x; i < NU; i += kCT) U[i] = 0ull;
     pt = 1;
     __syncthreads();
     return len;
@@ -619,16 +620,23 @@ constexpr uint64_t kLbAgg = 1ull << 62, kLbInc = 2ull << 62,
                    kLbVal = (1ull << 62) - 1;
 
 // ------------------------------------------------------------------ encoder
-// Record byte r of a chunk: 16-byte header, then the bins part, the subbin
-// part and zero padding to a multiple of 4.
-__device__ __forceinline__ uint8_t record_byte(uint32_t r, const uint8_t* hdr,
-                                               const uint8_t* bp, uint32_t blen,
-                                               const uint8_t* sp, uint32_t slen) {
-  if (r < kRecordHeaderBytes) return hdr[r];
-  r -= kRecordHeaderBytes;
-  if (r < blen) return bp[r];
-  r -= blen;
-  return r < slen ? sp[r] : (uint8_t)0;
+// Word q of a chunk's record: 16-byte header, then the bins part (blen bytes at
+// bp), the subbin part (slen at sp) and zero padding to a multiple of 4.  Reads
+// at most one word past either part.
+__device__ __forceinline__ uint32_t record_word(uint32_t q, const uint32_t* hdr,
+                                                const uint32_t* bp, uint32_t blen,
+                                                const uint32_t* sp, uint32_t slen) {
+  if (q < kRecordHeaderBytes / 4) return hdr[q];
+  const uint32_t r = 4 * q - kRecordHeaderBytes;
+  if (r + 4 <= blen) return bp[r / 4];
+  auto low = [](uint32_t v, uint32_t n) { return n < 4 ? v & ((1u << (8 * n)) - 1u) : v; };
+  if (r < blen) {  // the bins part's last bytes, the subbin part's first
+    const uint32_t k = blen - r;
+    return low(bp[r / 4], k) | low(sp[0], slen) << (8 * k);
+  }
+  const uint32_t o = r - blen;
+  if (o >= slen) return 0;
+  return low(__builtin_amdgcn_alignbyte(sp[o / 4 + 1], sp[o / 4], o & 3), slen - o);
 }
 
 // Where the record of chunk c of a single field waits for its offset: the
@@ -675,15 +683,10 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   using Word = typename Tr::Word;
   constexpr uint32_t W = kChunkBytes / K;
   constexpr int PER = (int)(W / kCT);  // consecutive words of a thread
-  // LDS: the look-back path keeps the bins part (B) until the end beside
-  // the RZE_K output (X): 54,248 bytes, three workgroups per CU.  The slot
-  // path parks the bins part as soon as it is known and reuses B for X:
-  // about 37.9 KB, four workgroups per CU.
-  __shared__ uint64_t U[kMaxUnits];      // bit planes; later the subbin part
-  __shared__ uint64_t B[kMaxUnits + 2];  // bins part (slot path: then X)
-  __shared__ uint64_t Xb[kSlot ? 1 : kMaxUnits + 2];  // subbins after RZE_K
-  uint64_t* X = kSlot ? B : Xb;
-  __shared__ uint32_t s_btail;  // slot path: bytes of the bins part's partial last word
+  // LDS: both parts from bit planes to the end, 34 KB, so that four workgroups
+  // fill a CU's waves
+  __shared__ uint64_t B[kMaxUnits + 1];  // bins (and a word read past them)
+  __shared__ uint64_t U[kMaxUnits + 1];  // subbins
   __shared__ EncScratch sc;
   // the record header and the chunk's offset live in sc.orv, which is free
   // once the planes in use are known
@@ -762,29 +765,13 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
   const uint32_t npb = (uint32_t)__builtin_amdgcn_readfirstlane(
       orb ? 64 - __builtin_clzll(orb) : 0);
   const uint32_t nps = (uint32_t)__builtin_amdgcn_readfirstlane(ors ? 32 - __builtin_clz(ors) : 0);
-  // BIT_K, RZE_1
-  words_to_planes<K, PER>(wv, G, npb, U);
-  __syncthreads();
-  int pt_b = 0, pt_s1 = 0, pt_s2 = 0;
-  const uint32_t blen = rze_encode<1>(U, L, npb * G, (uint8_t*)B, sc, pt_b);
-  const bool last = c == nch - 1;
-  const uint32_t room = last ? S.tail_len : S.len[0] + S.len[1] + S.len[2];
-  if constexpr (kSlot) {
-    // park the whole words of the bins part now (record bytes from 16 on)
-    if (kRecordHeaderBytes + blen <= room)
-      for (uint32_t q = threadIdx.x; q < blen / 4; q += kCT)
-        *slot_word(S, c, last, kRecordHeaderBytes / 4 + q) = ((const uint32_t*)B)[q];
-    if (threadIdx.x == 0)
-      s_btail = (blen & 3u) ? ((const uint32_t*)B)[blen / 4] & ((1u << (8 * (blen & 3u))) - 1u)
-                            : 0u;
-    __syncthreads();  // B is free for the RZE_K output
-  }
-
-  // subbins: BIT_K, RZE_K, RZE_1
+  words_to_planes<K, PER>(wv, G, npb, B);
   words_to_planes<K, PER>(sv, G, nps, U);
   __syncthreads();
-  const uint32_t smid = rze_encode<K>(U, L, nps * G, (uint8_t*)X, sc, pt_s1);
-  const uint32_t slen = rze_encode<1>(X, smid, (smid + 7) / 8, (uint8_t*)U, sc, pt_s2);
+  int pt_b = 0, pt_s1 = 0, pt_s2 = 0;
+  const uint32_t blen = rze_encode<1>(B, L, npb * G, sc, pt_b);
+  const uint32_t smid = rze_encode<K>(U, L, nps * G, sc, pt_s1);
+  const uint32_t slen = rze_encode<1>(U, smid, (smid + 7) / 8, sc, pt_s2);
 
   const uint32_t size = record_size(blen, slen);
   if (threadIdx.x == 0) {
@@ -804,27 +791,11 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
         *(uint32_t*)(stream + kHeaderBytes + 4ull * c) = size;
     }
     __syncthreads();  // hdr
-    if (size <= room) {
-      // the header words, then from the bins part's partial word on (its
-      // bytes from s_btail), the subbin part and the padding
-      const uint8_t* bt = (const uint8_t*)&s_btail;
-      const uint8_t* sp = (const uint8_t*)U;
-      const uint32_t nfull = blen / 4, nw = size / 4 - nfull;
-      for (uint32_t e = threadIdx.x; e < nw; e += kCT) {
-        const uint32_t q = e < kRecordHeaderBytes / 4 ? e : e + nfull;
-        uint32_t w = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const uint32_t r = 4 * q + b;
-          uint32_t v;
-          if (r < kRecordHeaderBytes) v = hdr[r];
-          else if (r < kRecordHeaderBytes + blen) v = bt[r - kRecordHeaderBytes - 4 * nfull];
-          else if (r < kRecordHeaderBytes + blen + slen) v = sp[r - kRecordHeaderBytes - blen];
-          else v = 0;
-          w |= v << (8 * b);
-        }
-        *slot_word(S, c, last, q) = w;
-      }
+    const bool last = c == nch - 1;
+    if (size <= (last ? S.tail_len : S.len[0] + S.len[1] + S.len[2])) {
+      for (uint32_t q = threadIdx.x; q < size / 4; q += kCT)
+        *slot_word(S, c, last, q) = record_word(q, (const uint32_t*)hdr, (const uint32_t*)B, blen,
+                                                (const uint32_t*)U, slen);
     } else if (threadIdx.x == 0) {
       set_status(prm, ST_INTERNAL);
     }
@@ -886,15 +857,9 @@ __device__ __forceinline__ void encode_body(uint32_t n, const typename Traits<K>
     if (c == nch - 1) prm->stream_size = dst + size;
   }
   if (dst + size <= cap) {
-    const uint8_t* bp = (const uint8_t*)B;
-    const uint8_t* sp = (const uint8_t*)U;
-    for (uint32_t q = threadIdx.x; q < size / 4; q += kCT) {
-      uint32_t w = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        w |= (uint32_t)record_byte(4 * q + b, hdr, bp, blen, sp, slen) << (8 * b);
-      ((uint32_t*)(stream + dst))[q] = w;
-    }
+    for (uint32_t q = threadIdx.x; q < size / 4; q += kCT)
+      ((uint32_t*)(stream + dst))[q] = record_word(q, (const uint32_t*)hdr, (const uint32_t*)B,
+                                                   blen, (const uint32_t*)U, slen);
   } else if (threadIdx.x == 0) {
     set_status(prm, ST_CAPACITY);
   }
@@ -1562,13 +1527,20 @@ __global__ __launch_bounds__(kThreads) void k_finalize_c(const BatchDesc* bd, co
   if (gate_sweep > 0 && bd->bc->lens[gate_sweep % kRing]) return;
   BatchResult* res = bd->res;
   const uint32_t nj = bd->job0[kGroups];
-  for (uint32_t j = blockIdx.x * kThreads + threadIdx.x; j < nj; j += gridDim.x * kThreads) {
+  // a thread per word of a header (one thread's 64 dependent byte copies took
+  // 18 us)
+  constexpr uint32_t HW = kHeaderBytes / 4;
+  static_assert(offsetof(Params, header) % 4 == 0 && offsetof(BatchResult, header) % 4 == 0,
+                "headers are copied as words");
+  for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < nj * HW; i += gridDim.x * kThreads) {
+    const uint32_t j = i / HW, w = i % HW;
     const Job& J = jobs[j];
+    ((uint32_t*)res[j].header)[w] = ((const uint32_t*)J.prm->header)[w];
+    if (w) continue;
     const int st = status_of(J.prm->status);
     const uint64_t size = J.prm->stream_size;
     res[j].size = size;
     res[j].status = st;
-    for (int b = 0; b < (int)kHeaderBytes; ++b) res[j].header[b] = J.prm->header[b];
     if (J.out_size) *J.out_size = size;
     if (J.out_status) *J.out_status = st;
   }
