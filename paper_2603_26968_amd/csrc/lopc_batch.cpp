@@ -547,8 +547,8 @@ int lopc_compress_batch(lopc_ctx* ctx, int n, const lopc_job* jobs, void* d_ws,
     HIP_CTX(ctx, launch_finalize_c(bd, dj, 0, hs));
     if (int st = read_back(ctx, P, ws, n, hs)) return st;
     if (!ctx->graph_sweeps) {
-      int h = 16;
-      while (h < (int)sweeps + 1 && h < kMaxGraphSweeps) h *= 2;
+      // in steps of 8: a captured sweep that finds nothing takes 4.5 us
+      const int h = std::max(16, ((int)sweeps + 8) / 8 * 8);
       ctx->sweeps_hint = std::min(h, kMaxGraphSweeps);
     }
   }
