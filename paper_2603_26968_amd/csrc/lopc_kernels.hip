@@ -1263,6 +1263,10 @@ __device__ __forceinline__ int64_t first_bin(double y, double inv, bool& bad) {
 // carry.  The neighbour tiles to sweep next are found at the end from the
 // face points: those with a same-bin lower neighbour in the tile that rose and
 // would raise them.
+// Bound by vector issue in 3D (0.7 to 0.8 of its rate), by the chains of its
+// rounds in 2D: 512^3 binary64 2 x 2.69 -> 2 x 1.85 ms, 256^3 binary32 147 ->
+// 128 us, 1800 x 3600 binary32 167 -> 119 us against flags from both keys and
+// bins per neighbour and passes to the end.
 constexpr int32_t kNoBin = (int32_t)0x80000000;
 template <int NPT>
 struct ReadyLds {
