@@ -1146,10 +1146,10 @@ __device__ bool q_claim(const QueueRef& Q, uint32_t t, const TileCoord& c, const
   return true;
 }
 
-// End of a run of tile t (wave 0 of its block): list the neighbour tiles in
-// `dirs` (27-bit set, see out_dirs) after releasing the block's subbin
-// stores, stop running, publish the tiles parked on t, and stop counting
-// the run as pending.
+// End of a run of tile t (wave 0 of its block, whose waves have each released
+// their subbin stores before the block's last barrier): list the neighbour
+// tiles in `dirs` (27-bit set, see out_dirs), stop running, publish the tiles
+// parked on t, and stop counting the run as pending.
 __device__ void q_finish(uint32_t dirs, uint32_t t, const TileCoord& c, const Tiling& tl,
                          const QueueRef& Q, uint32_t t0, uint32_t depth) {
   if (dirs) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -1709,6 +1709,10 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
       }
     }
   }
+  // queue mode: every wave's subbins have to be out before wave 0, past the
+  // barriers below, lets the tile go (q_finish), as its next run, on whatever
+  // XCD, starts from them; a barrier alone does not wait for stores
+  if (QM) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   if (QM && blockers) {
     const uint64_t both = block_or64((uint64_t)ups << 32 | dirs);
     if (threadIdx.x == 0) blockers[t] = (uint32_t)(both >> 32) & ~0x3fffu;
