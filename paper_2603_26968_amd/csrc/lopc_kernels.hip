@@ -1130,6 +1130,7 @@ __device__ bool q_claim(const QueueRef& Q, uint32_t t, const TileCoord& c, const
     while (bl) {
       const int d = 31 - __builtin_clz(bl);  // the farthest in index first
       bl &= ~(1u << d);
+      if (!dir_inside(d, c, tl)) continue;
       const uint32_t v = dir_tile(d, c, tl, t0);
       if (!(__hip_atomic_load(&Q.st[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
             (TS_LISTED | TS_RUNNING)))
@@ -1222,33 +1223,6 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t m, uint64_t a, uint64_t b)
   return r;
 }
 
-// Bin of value y in the first pass (Sec. IV-A): q_bin / q_bin32 with the
-// common case branch-free.  float32: the conversion saturates, so a product
-// out of range gives a bin outside the limits.  float64: below 2^51 the
-// rounded product plus 1.5 * 2^52 holds the integer in its low bits.
-template <int K>
-__device__ __forceinline__ int64_t first_bin(double y, double inv, bool& bad) {
-  const double p = y * inv;
-  double q = rint(p);
-  if (fabs(p - q) == 0.5) {
-    const double r = fma(y, inv, -p);
-    if (r != 0.0) q = r > 0.0 ? p + 0.5 : p - 0.5;
-  }
-  if constexpr (K == 4) {
-    int32_t b;
-    asm("v_cvt_i32_f64 %0, %1" : "=v"(b) : "v"(q));
-    bad |= (uint32_t)b + 0x7ffffffeu > 0xfffffffcu;  // |b| > 2^31 - 2
-    return b;
-  } else {
-    int64_t b = __double_as_longlong(q + 6755399441055744.0) - 0x4338000000000000ll;
-    if (!(fabs(p) < 2251799813685248.0)) {
-      b = q_bin(y, inv);
-      bad |= b > Traits<8>::kBinLimit || b < -Traits<8>::kBinLimit;
-    }
-    return b;
-  }
-}
-
 // First pass of a tile, fused: quantize (a1), the order flags of the owned
 // points (a2, the flags of Alg. 1), and the first relaxation (the first sweep
 // of a3) with halo subbins 0 or, for hc >= 0, those of the neighbour tiles of
@@ -1267,7 +1241,6 @@ __device__ __forceinline__ int64_t first_bin(double y, double inv, bool& bad) {
 // rounds in 2D: 512^3 binary64 2 x 2.69 -> 2 x 1.85 ms, 256^3 binary32 147 ->
 // 128 us, 1800 x 3600 binary32 167 -> 119 us against flags from both keys and
 // bins per neighbour and passes to the end.
-constexpr int32_t kNoBin = (int32_t)0x80000000;
 template <int NPT>
 struct ReadyLds {
   uint16_t list[NPT];
@@ -1394,8 +1367,7 @@ __device__ __forceinline__ uint32_t tile0_body(
     for (int j = NJ - 1; j >= 0; --j) {
       const int ln = li + kOff[j][0] * HXY + kOff[j][1] * G::HX + kOff[j][2];
       const Val vq = X[ln];
-      // odd j: the neighbour has the lower index
-      m = shift_in(m, __ballot(B[ln] == bo[k]), __ballot((j & 1) ? vq <= vp : vq < vp));
+      m = shift_in(m, __ballot(B[ln] == bo[k]), __ballot(flag_lower(j, vq, vp)));
     }
     if (wide && in(k)) {
       uint32_t lm = 0;

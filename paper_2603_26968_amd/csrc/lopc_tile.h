@@ -1,5 +1,6 @@
 // Geometry of the repair's tiles: the LDS box of a tile and its one-point
-// halo, and the halo points a run needs, face by face.  Host+device so that a
+// halo, and the halo points a run needs, face by face; and the bins and
+// comparisons the first pass makes its order flags of.  Host+device so that a
 // CPU harness can check the same source.
 #pragma once
 
@@ -127,5 +128,54 @@ struct Blind {
     return (z + G::ZO) * G::HY * G::HX + (i < TZ ? G::HX - 1 : (G::HY - 1) * G::HX);
   }
 };
+
+// ------------------------------------------------------------------ flags
+// The first pass compares the bins of neighbours in 32 bits.  A cell outside
+// the grid holds kNoBin, a bin that no point has, so that no comparison needs
+// a bounds check.
+constexpr int32_t kNoBin = (int32_t)0x80000000;
+
+// Bin of value y in the first pass (Sec. IV-A): q_bin / q_bin32 with the
+// common case branch-free.  float32: the conversion saturates, so a product
+// out of range gives a bin outside the limits, of which the lowest is raised
+// by one to leave kNoBin free.  float64: below 2^51 the rounded product plus
+// 1.5 * 2^52 holds the integer in its low bits.
+template <int K>
+LOPC_HD int64_t first_bin(double y, double inv, bool& bad) {
+  const double p = y * inv;
+  double q = rint(p);
+  if (fabs(p - q) == 0.5) {
+    const double r = fma(y, inv, -p);
+    if (r != 0.0) q = r > 0.0 ? p + 0.5 : p - 0.5;
+  }
+  if constexpr (K == 4) {
+    int32_t b;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(b) : "v"(q));
+#else
+    b = q >= 2147483647.0    ? 0x7fffffff
+        : q <= -2147483648.0 ? (int32_t)0x80000000
+        : q == q             ? (int32_t)q
+                             : 0;
+#endif
+    b = b < -0x7fffffff ? -0x7fffffff : b;
+    bad |= (uint32_t)b + 0x7ffffffeu > 0xfffffffcu;  // |b| > 2^31 - 2
+    return b;
+  } else {
+    int64_t b = (int64_t)__builtin_bit_cast(uint64_t, q + 6755399441055744.0) - 0x4338000000000000ll;
+    if (!(fabs(p) < 2251799813685248.0)) {
+      b = q_bin(y, inv);
+      bad |= b > Traits<8>::kBinLimit || b < -Traits<8>::kBinLimit;
+    }
+    return b;
+  }
+}
+
+// Of two neighbours in one bin, whether vq, at stencil offset j of vp, is the
+// lower in (value, index) order: an odd j has the lower index.
+template <typename Val>
+LOPC_HD bool flag_lower(int j, Val vq, Val vp) {
+  return (j & 1) ? vq <= vp : vq < vp;
+}
 
 }  // namespace lopc
