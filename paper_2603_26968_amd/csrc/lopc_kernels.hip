@@ -428,6 +428,13 @@ __device__ __forceinline__ uint32_t pull_best(const uint32_t* P, int li, uint32_
 // hands over to event rounds.
 template <int NPT>
 constexpr uint32_t kEventShare = NPT / 16;
+// Cost of the events of a 2D run after which the rest of it goes by levels
+// (whole_run): a round of few events counts 1 (0.31 us), 64 events of another 3.
+// A run by levels takes 5 us and 0.1 us a level.  us a call at 24 / 36 / 48:
+// 2048^2 bumps at bound 1e-2 353 / 308 / 313, 1800 x 3600 fronts at 1e-3 359 /
+// 352 / 352, at 1e-1 1,907 / 1,997 / 2,100; with no limit and passes after full
+// lists 302, 366 and 8,830.
+constexpr uint32_t kEventCost = 36;
 // Events of a round up to which each gets a lane per neighbour.
 constexpr uint32_t kNarrow = 32;
 // Workgroups of a single-field sweep that expects few marked tiles: the six of
@@ -440,7 +447,7 @@ template <int NPT>
 struct EventLds {
   static constexpr uint32_t kCap = NPT / kWaves;  // entries of one list: a wave's slots
   uint16_t list[kWaves][2][kCap];
-  uint32_t over;     // a list was full: points were not listed
+  uint32_t over;     // points were left out of a full list, or the events cost too much
   uint32_t big;      // a loaded subbin exceeds kPackMax
   uint32_t dirs;     // neighbour tiles to mark (27-direction set)
   uint32_t rose[3];  // points raised by pass p in slot p % 3
@@ -494,7 +501,8 @@ __device__ __forceinline__ void list_risen(EventLds<NPT>& E, uint16_t* list, uin
 // LDS maxima issued together.  Rounds of few events give each event a lane per
 // neighbour instead of a lane in all.  Halo words rise too (kRose marks them),
 // but push nothing.  A point raised twice in a round is listed twice (its
-// second event finds nothing to raise).  Returns the rounds.
+// second event finds nothing to raise).  Sets E.over and leaves off where the
+// events cost more than the other way (2D, kEventCost).  Returns the rounds.
 // Bound by vector issue on large fields and by the latency of the rounds on
 // small ones.  Against passes over all points until none rises: the 24 sweep
 // launches on a 512^3 float64 lognormal field 8.3 -> 6.1 ms (vector
@@ -512,7 +520,15 @@ __device__ __forceinline__ int push_rounds(uint32_t* P, EventLds<TZ * TY * TX>& 
   const int offl = jl < NJ ? off_lin(jl, HX, HXY) : 0;
   const uint32_t keepl = 0xffffu | 1u << (16 + ((jl < NJ ? jl : 0) ^ 1));
   int r = 0;
+  uint32_t cost = 0;
   while (n) {
+    if constexpr (TZ == 1) {
+      cost += n > kNarrow ? 3 * ((n + 63) / 64) : 1u;
+      if (cost > kEventCost) {
+        E.over = 1;
+        break;
+      }
+    }
     const uint16_t* in = E.list[w][r & 1];
     uint16_t* out = E.list[w][(r + 1) & 1];
     uint32_t made = 0;
@@ -611,8 +627,8 @@ __device__ __forceinline__ void count_rose(EventLds<NPT>& E, uint32_t changed, i
 // Passes until no owned point rises (after a full event list).  Every thread
 // calls it past a block barrier; returns the passes.
 template <int TZ, int TY, int TX>
-__device__ __noinline__ int word_passes(uint32_t* P, EventLds<TZ * TY * TX>& E,
-                                        uint32_t* counters) {
+__device__ __forceinline__ int word_passes(uint32_t* P, EventLds<TZ * TY * TX>& E,
+                                           uint32_t* counters) {
   using G = TileGeom<TZ, TY, TX>;
   if (threadIdx.x < 3) E.rose[threadIdx.x] = 0;
   __syncthreads();
@@ -795,11 +811,11 @@ __device__ void relax(uint32_t* P, EventLds<TZ * TY * TX>& E, const uint16_t* mk
 }
 
 // Local fixed point of a tile whose subbins may not fit the 16 bits of an LDS
-// word: passes over the owned points (S: subbins, 32 bits; mk: flags), slots
-// in alternating order, until none rises.
+// word: passes over the owned points (S: subbins, 32 bits; M: flags), slots in
+// alternating order, until none rises.  Returns the passes.
 template <int TZ, int TY, int TX>
-__device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
-                           unsigned long long* itot, uint32_t t) {
+__device__ __forceinline__ int relax_wide(uint32_t* S, const uint16_t* M,
+                                          uint32_t* counters) {
   using G = TileGeom<TZ, TY, TX>;
   constexpr int NJ = TZ == 1 ? 6 : 14;
   const int li0 = G::local(threadIdx.x);
@@ -815,9 +831,9 @@ __device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
 #pragma unroll 1
     for (int kk = 0; kk < G::PER; ++kk) {
       const int k = rev ? G::PER - 1 - kk : kk;
-      const uint32_t m = mk[k];
-      if (!m) continue;
       const int li = li0 + k * G::kSlot;
+      const uint32_t m = M[li];
+      if (!m) continue;
       const uint32_t cur = S[li];
       const uint32_t best = dense_best<NJ, G::HX, G::HY * G::HX>(S, li, m, cur);
       if (best > cur) {
@@ -833,7 +849,7 @@ __device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
       break;
     }
   }
-  if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)(iters + 1));
+  return iters + 1;
 }
 
 // ------------------------------------------------------------------ peeling
@@ -844,7 +860,7 @@ __device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
 // ready once all its lower neighbours inside the tile are done, and then takes
 // its final value at once (the raising rule of Alg. 2 for a fixed halo).
 // The LDS word of an owned point counts its unfinished lower neighbours inside
-// the tile in bits 22..24.  A ready point reads its six neighbours' words at
+// the tile in bits 22..24, and holds its level in bits 22..29 once it is done.  A ready point reads its six neighbours' words at
 // once (one LDS round trip): its own raise from those its flags name, and the
 // dependents, whose flags name it, are counted down by LDS atomics issued
 // together; those that reach zero are listed for the next level.  The list
@@ -852,6 +868,13 @@ __device__ void relax_wide(uint32_t* S, const uint16_t* mk, uint32_t* counters,
 // run on wave 0 alone without block barriers.  Returns the levels of this
 // wave; ends with a block barrier.
 constexpr int kLeftShift = 22;
+// In memory the order flags of a 2D point (six bits) share their 16 bits with
+// its level inside its tile (255: that or more).
+constexpr int kLevelShift = 8;
+template <int TZ>
+__device__ __forceinline__ uint32_t flags_of(uint32_t m) {
+  return TZ == 1 ? m & 0x3fu : m;
+}
 template <int TZ, int TY, int TX>
 __device__ __forceinline__ int peel(uint32_t* P, uint16_t* list, uint32_t* tail) {
   using G = TileGeom<TZ, TY, TX>;
@@ -894,7 +917,8 @@ __device__ __forceinline__ int peel(uint32_t* P, uint16_t* list, uint32_t* tail)
       for (int j = 0; j < NJ; ++j)
         c[j] = and_word(q[j], (uint32_t)((int32_t)(m << (31 - j)) >> 31));
       const uint32_t best = fold_cands<NJ>(c, m, wp & 0xffffu);
-      if (act) P[p] = (wp & 0xffff0000u) | best;
+      if (act)
+        P[p] = (wp & 0xffff0000u) | best | (uint32_t)min(level, 255) << kLeftShift;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         // neighbour j names p in its flag j ^ 1 (clear) and lies in the tile
@@ -1384,8 +1408,8 @@ __device__ __forceinline__ uint32_t tile0_body(
       m = lm;
     }
     mk[k] = in(k) ? (uint16_t)m : (uint16_t)0;
-    if (in(k)) mask[g0 + k * gstep] = (uint16_t)m;
     if constexpr (TZ > 1) {
+      if (in(k)) mask[g0 + k * gstep] = (uint16_t)m;
       P[li] = kNoFlags & ~((uint32_t)mk[k] << 16);
     } else {
       // the count of lower neighbours inside the tile
@@ -1410,7 +1434,12 @@ __device__ __forceinline__ uint32_t tile0_body(
   }
 #pragma unroll
   for (int k = 0; k < PZ; ++k)
-    if (in(k)) sub[g0 + k * gstep] = P[li0 + k * G::kSlot] & 0xffffu;
+    if (in(k)) {
+      const uint32_t v = P[li0 + k * G::kSlot];
+      sub[g0 + k * gstep] = v & 0xffffu;
+      if constexpr (TZ == 1)
+        mask[g0 + k * gstep] = (uint16_t)(mk[k] | (v >> kLeftShift & 0xffu) << kLevelShift);
+    }
   uint32_t dirs = 0;
 #pragma unroll
   for (int q = 0; q < F::kPer; ++q) {
@@ -1506,8 +1535,257 @@ template <int TZ, int TY, int TX>
 struct RunLds {
   uint32_t P[TileGeom<TZ, TY, TX>::H];  // LDS words (32-bit way: subbins)
   EventLds<TZ * TY * TX> E;
+  alignas(16) uint32_t hist[TZ == 1 ? 256 : 4];  // 2D: points of each level
   uint32_t go;
 };
+
+// The owned points of a 2D tile level by level (P: LDS words; WIDE: subbins
+// in 32 bits; flags(k): those of slot k): a point's level is the longest path
+// of its lower neighbours inside the tile, kept by the first pass (level(k)),
+// so one visit in this order, the halo fixed, gives every point its final
+// value.  The points with flags are sorted into `list` (a counting sort; LDS
+// index, flags and level to an entry), then the first wave takes them, up to 64
+// of one level at a time: per step one LDS round trip, with the next entries
+// already on their way, no atomics and no barriers.  Returns the steps
+// (block-uniform), -1 before it has touched P if a level is not known (255).
+template <int TZ, int TY, int TX, bool WIDE, typename Flags, typename Level>
+__device__ __forceinline__ int level_run(RunLds<TZ, TY, TX>& lds, int tid, const Flags& flags,
+                                         const Level& level) {
+  using G = TileGeom<TZ, TY, TX>;
+  static_assert(TZ == 1, "2D tiles");
+  constexpr int NJ = 6, HX = G::HX, HXY = G::HY * G::HX;
+  uint32_t* const P = lds.P;
+  uint32_t* const list = (uint32_t*)&lds.E.list[0][0][0];
+  static_assert(sizeof(lds.E.list) >= G::NPT * 4 && G::H <= 4096, "the entries fit");
+  uint32_t* const unknown = &lds.E.rose[0];
+  uint32_t lv[G::PER / 4] = {};  // four levels to a word
+#pragma unroll
+  for (int k = 0; k < G::PER; ++k) lv[k / 4] |= level(k) << (8 * (k % 4));
+  static_assert(kThreads == 256 && G::PER % 4 == 0, "a counter per thread");
+  lds.hist[tid] = 0;
+  if (tid == 0) *unknown = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < G::PER; ++k) {
+    const uint32_t l = (lv[k / 4] >> (8 * (k % 4))) & 255u;
+    if (flags(k)) {
+      if (l == 255u) *unknown = 1;
+      atomicAdd(&lds.hist[l], 1u);
+    }
+  }
+  __syncthreads();
+  const bool none = *unknown != 0;
+  // the counts become starts
+  if (tid < 64) {
+    const uint4 v = ((const uint4*)lds.hist)[tid & 63];
+    const uint32_t t = v.x + v.y + v.z + v.w, b = wave_scan_u32(t) - t;
+    ((uint4*)lds.hist)[tid & 63] = make_uint4(b, b + v.x, b + v.x + v.y, b + v.x + v.y + v.z);
+  }
+  __syncthreads();
+  if (none) return -1;
+  // no point has level 255: its start is the number of points
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds.hist[255]);
+#pragma unroll
+  for (int k = 0; k < G::PER; ++k) {
+    const uint32_t l = (lv[k / 4] >> (8 * (k % 4))) & 255u, f = flags(k);
+    if (f)
+      list[atomicAdd(&lds.hist[l], 1u)] =
+          (uint32_t)(G::local(tid) + k * G::kSlot) | f << 12 | l << 18;
+  }
+  __syncthreads();
+  int steps = 0;
+  if (tid < 64) {
+    uint32_t pos = 0, ent = list[tid & 63];
+    while (pos < total) {
+      const uint32_t l0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ent >> 18));
+      const uint64_t other = ~__ballot((ent >> 18) == l0 && pos + (uint32_t)(tid & 63) < total);
+      const uint32_t n = other ? (uint32_t)__builtin_ctzll(other) : 64u;
+      pos += n;
+      const uint32_t next = list[min(pos + (uint32_t)(tid & 63), (uint32_t)G::NPT - 1u)];
+      const bool act = (uint32_t)(tid & 63) < n;
+      const int li = act ? (int)(ent & 4095u) : G::local(0);
+      const uint32_t f = (ent >> 12) & 0x3fu, wd = P[li];
+      uint32_t q[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) q[j] = P[li + kOff[j][0] * HXY + kOff[j][1] * HX + kOff[j][2]];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const uint32_t on = (uint32_t)((int32_t)(f << (31 - j)) >> 31);
+        q[j] = WIDE ? q[j] & on : and_word(q[j], on);
+      }
+      const uint32_t cur = WIDE ? wd : wd & 0xffffu;
+      const uint32_t best = fold_cands<NJ>(q, f, cur);
+      if (act && best > cur) P[li] = WIDE ? best : (wd + (best - cur)) | kRose;
+      ent = next;
+      ++steps;
+    }
+  }
+  __syncthreads();
+  return steps;
+}
+
+// End of a tile run: the neighbour tiles of the lanes' dirs (27-direction set),
+// block-uniform; with `blockers` (queue mode), thread 0 stores there those of
+// higher index in `ups`.
+template <bool QM, int NPT>
+__device__ __forceinline__ uint32_t end_run(EventLds<NPT>& E, uint32_t dirs, uint32_t ups,
+                                            uint32_t* blockers, uint32_t t) {
+  // queue mode: every wave's subbins have to be out before wave 0, past the
+  // barriers below, lets the tile go (q_finish), as its next run, on whatever
+  // XCD, starts from them; a barrier alone does not wait for stores
+  if (QM) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  if (QM && blockers) {
+    const uint64_t both = block_or64((uint64_t)ups << 32 | dirs);
+    if (threadIdx.x == 0) blockers[t] = (uint32_t)(both >> 32) & ~0x3fffu;
+    return (uint32_t)both;
+  }
+  if (__ballot(dirs != 0u)) {
+    dirs = wave_reduce(dirs, OpOr{});
+    if (lane() == 0) atomicOr(&E.dirs, dirs);
+  }
+  __syncthreads();
+  return E.dirs;
+}
+
+// The rest of a tile run over all of its points instead of events (2D by
+// levels, else by passes): after more events than that takes (the words in LDS
+// as the events left them), or, `wide`, from the start with 32-bit subbins.
+// Its loops are rolled up and start from the thread's place alone (opaque), so
+// that inlined it leaves the sweeps the registers of their event runs (3D 49,
+// 2D 56; unrolled and called 87 and 100, rolled up and called 74 and 87).
+// Bound by the chain of its steps.  Against events and passes to the end: 1800
+// x 3600 fronts at bound 1e-2 2,250 -> 715 us a call, at 1e-1 8,830 -> 2,025, at
+// 1e0 19,050 -> 7,160.
+template <int TZ, int TY, int TX, bool QM>
+__device__ __forceinline__ uint32_t whole_run(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
+                                           const uint16_t* __restrict__ mask,
+                                           uint32_t* __restrict__ sub, uint32_t* counters,
+                                           unsigned long long* itot, uint32_t t,
+                                           uint32_t* blockers, bool wide) {
+  using G = TileGeom<TZ, TY, TX>;
+  using F = Faces<TZ, TY, TX>;
+  constexpr int NJ = TZ == 1 ? 6 : 14, HXY = G::HY * G::HX;
+  int tid = (int)threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  __builtin_assume(tid >= 0 && tid < kThreads);
+  uint32_t* const P = lds.P;
+  const TileCoord c = tile_coord<TZ, TY, TX>(t, tl);
+  const int w = __builtin_amdgcn_readfirstlane(wave());
+  const int li0 = G::local(tid);
+  const int64_t g00 = ((int64_t)c.z0 * box.ny + c.y0) * box.nx + c.x0;
+  // slot k's offset from the tile's first point (that point's if outside)
+  constexpr int kRows = TZ > 1 ? 1 : kThreads / TX;
+  const int iy = tid / TX, ix = tid % TX;
+  const bool in0 = c.x0 + ix < box.nx;
+  auto in = [&](int k) {
+    return in0 && (TZ > 1 ? c.y0 + iy < box.ny && c.z0 + k < box.nz
+                          : c.y0 + iy + k * kRows < box.ny);
+  };
+  auto at = [&](int k) -> int64_t {
+    const int64_t step = TZ > 1 ? (int64_t)box.ny * box.nx : (int64_t)kRows * box.nx;
+    return in(k) ? g00 + (int64_t)iy * box.nx + ix + k * step : g00;
+  };
+  auto load = [&](int64_t g) {
+    return QM ? __hip_atomic_load(sub + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : sub[g];
+  };
+  auto store = [&](int64_t g, uint32_t v) {
+    if (QM) __hip_atomic_store(sub + g, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else sub[g] = v;
+  };
+  auto level = [&](int k) { return (uint32_t)mask[at(k)] >> kLevelShift; };
+  auto flags = [&](int k) {
+    const uint32_t m = flags_of<TZ>(mask[at(k)]);
+    return in(k) ? m : 0u;
+  };
+  uint32_t dirs = 0, ups = 0;
+  if (QM && blockers) {
+#pragma unroll 1
+    for (int k = 0; k < G::PER; ++k) {
+      const int i = tid + k * kThreads;
+      const uint32_t m = flags(k);
+      if (m && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, m);
+    }
+  }
+  int steps = -1;
+  if (!wide) {
+    if constexpr (TZ == 1)
+      steps = level_run<TZ, TY, TX, false>(
+          lds, tid, [&](int k) { return (~P[li0 + k * G::kSlot] >> 16) & 0x3fu; }, level);
+    if (steps < 0) steps = word_passes<TZ, TY, TX>(P, lds.E, counters);
+    // the face points that an event raised or a risen point of the tile would
+#pragma unroll 1
+    for (int s = w; s < F::kSlots; s += kWaves) {
+      const FaceSlot& f = kFaces<TZ, TY, TX>.s[s];
+      const FacePoint p = face_point(f, tid & 63, c, box, g00);
+      if (!p.in) continue;
+      const uint32_t h = P[p.li], wt = 1u - f.weight;
+      bool up = (h & kRose) != 0;
+#pragma unroll
+      for (int k = 0; k < F::ND; ++k) {
+        // the flag through which the face point sees the tile's point is the
+        // one the point sees it through, from the other end
+        const uint32_t x = P[p.li + f.d[k]], seen = f.keep[k] & kNoFlags;
+        up |= (x & (kHalo | kRose)) == kRose && !(h & (f.weight ? seen << 1 : seen >> 1)) &&
+              (x & 0xffffu) + wt > (h & 0xffffu);
+      }
+      if (up) dirs |= cell_dir<TZ, TY, TX>(p.li);
+    }
+#pragma unroll 1
+    for (int k = 0; k < G::PER; ++k) {
+      const uint32_t v = P[li0 + k * G::kSlot];
+      if (v & kRose) store(at(k), v & 0xffffu);
+    }
+  } else {
+    __syncthreads();  // the words have been read
+#pragma unroll 2
+    for (int k = 0; k < G::PER; ++k) {
+      const uint32_t v = load(at(k));
+      P[li0 + k * G::kSlot] = in(k) ? v : 0u;
+    }
+#pragma unroll 1
+    for (int s = w; s < F::kSlots; s += kWaves) {
+      const FacePoint p = face_point(kFaces<TZ, TY, TX>.s[s], tid & 63, c, box, g00);
+      if (p.li >= 0) P[p.li] = p.in ? load(p.g) : 0u;
+    }
+    __syncthreads();
+    // the flags of the owned and the face points
+    uint16_t* const M = &lds.E.list[0][0][0];
+    static_assert(sizeof(lds.E.list) >= G::H * 2, "the flags fit the event lists");
+#pragma unroll 2
+    for (int k = 0; k < G::PER; ++k) M[li0 + k * G::kSlot] = (uint16_t)flags(k);
+#pragma unroll 1
+    for (int s = w; s < F::kSlots; s += kWaves) {
+      const FacePoint p = face_point(kFaces<TZ, TY, TX>.s[s], tid & 63, c, box, g00);
+      if (p.li >= 0) M[p.li] = p.in ? (uint16_t)flags_of<TZ>(mask[p.g]) : (uint16_t)0;
+    }
+    if (steps < 0) steps = relax_wide<TZ, TY, TX>(P, M, counters);
+    else __syncthreads();  // M
+#pragma unroll 1
+    for (int k = 0; k < G::PER; ++k) {
+      const int i = tid + k * kThreads, li = li0 + k * G::kSlot;
+      const uint32_t v = P[li];
+      const int64_t g = at(k);
+      if (!in(k) || v == load(g)) continue;
+      store(g, v);
+      if (!G::on_edge(i)) continue;
+      // halo neighbours whose flags name this point (offset j from here is
+      // offset j ^ 1 from there)
+      const int pz = i / (TY * TX), py = (i / TX) % TY, px = i % TX;
+      uint32_t dep = 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int z = pz + kOff[j][0], y = py + kOff[j][1], x = px + kOff[j][2];
+        if (z < 0 || z >= TZ || y < 0 || y >= TY || x < 0 || x >= TX)
+          dep |= (uint32_t)((M[li + kOff[j][0] * HXY + kOff[j][1] * G::HX + kOff[j][2]] >>
+                             (j ^ 1)) & 1u) << j;
+      }
+      if (dep) dirs |= out_dirs<TZ, TY, TX>(i, dep);
+    }
+  }
+  if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)steps);
+  return end_run<QM>(lds.E, dirs, ups, blockers, t);
+}
+
 template <int TZ, int TY, int TX, bool QM = false, bool LOOP = false>
 __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
                             const uint16_t* __restrict__ mask, uint32_t* __restrict__ sub,
@@ -1516,13 +1794,8 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
                             uint32_t* blockers = nullptr) {
   using G = TileGeom<TZ, TY, TX>;
   using F = Faces<TZ, TY, TX>;
-  constexpr int NJ = TZ == 1 ? 6 : 14;
-  constexpr int HXY = G::HY * G::HX;
   uint32_t* const P = lds.P;
   EventLds<G::NPT>& E = lds.E;
-  // flags of the halo and the owned points (32-bit way)
-  uint16_t* M = &E.list[0][0][0];
-  static_assert(sizeof(E.list) >= G::H * 2, "the flags fit the event lists");
   // one read decides for the whole block (a neighbour may raise the stamp
   // concurrently)
   if (threadIdx.x == 0) {
@@ -1539,7 +1812,10 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
   int tid = (int)threadIdx.x;
   if (LOOP) asm volatile("" : "+v"(tid));
   __builtin_assume(tid >= 0 && tid < kThreads);
+  // (the face slots are a multiple of the waves for the default shapes: no
+  // branch then stands between their loads)
   const int w = __builtin_amdgcn_readfirstlane(wave());
+  __builtin_assume(w >= 0 && w < kWaves);
   const int li0 = G::local(tid);
   const int64_t nyx = (int64_t)box.ny * box.nx;
   const int64_t g00 = ((int64_t)c.z0 * box.ny + c.y0) * box.nx + c.x0;  // the tile's first point
@@ -1557,7 +1833,7 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
       v = QM ? __hip_atomic_load(sub + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : sub[g];
       m = mask[g];
       v = in ? v : 0u;
-      m = in ? m : (uint16_t)0;
+      m = in ? (uint16_t)flags_of<TZ>(m) : (uint16_t)0;
     };
 #pragma unroll
     for (int k = 0; k < G::PER; ++k) {
@@ -1594,108 +1870,49 @@ __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box
     __syncthreads();
     wide = E.big;
   }
-  uint32_t dirs = 0, ups = 0;
-  if (wide) {
-    __syncthreads();
+  if (__builtin_expect(wide, 0)) return whole_run<TZ, TY, TX, QM>(lds, box, tl, mask, sub, counters, itot, t, blockers, true);
+  // the face points push into the tile
+  uint32_t n = 0;
 #pragma unroll
-    for (int k = 0; k < G::PER; ++k) {
-      P[li0 + k * G::kSlot] = ov[k];
-      M[li0 + k * G::kSlot] = om[k];
-    }
+  for (int q = 0; q < F::kPer; ++q) {
+    if (w + q * kWaves >= F::kSlots) continue;
+    const FaceSlot& f = kFaces<TZ, TY, TX>.s[w + q * kWaves];
+    const uint32_t nv = hl[q] >= 0 ? hv[q] + f.weight : 0u;
+    const int l = hl[q] >= 0 ? hl[q] : f.li;
+    uint32_t x[F::ND], old[F::ND];
 #pragma unroll
-    for (int q = 0; q < F::kPer; ++q) {
-      if (hl[q] >= 0) {
-        P[hl[q]] = hv[q];
-        M[hl[q]] = hm[q];
-      }
-    }
-    __syncthreads();
-    relax_wide<TZ, TY, TX>(P, om, counters, itot, t);
+    for (int k = 0; k < F::ND; ++k) x[k] = P[l + f.d[k]];
 #pragma unroll
-    for (int k = 0; k < G::PER; ++k) {
-      const int i = tid + k * kThreads;
-      const int li = G::local(i);
-      const uint32_t v = P[li];
-      if (QM && blockers && om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
-      if (v == ov[k]) continue;
-      if (QM) __hip_atomic_store(sub + og[k], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else sub[og[k]] = v;
-      if (!G::on_edge(i)) continue;
-      // halo neighbours whose flags name this point (offset j from here is
-      // offset j ^ 1 from there)
-      const int iz = i / (TY * TX), iy = (i / TX) % TY, ix = i % TX;
-      uint32_t dep = 0;
+    for (int k = 0; k < F::ND; ++k)
+      old[k] = raise_word(&P[l + f.d[k]], (x[k] & f.keep[k]) < nv, x[k], nv);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int z = iz + kOff[j][0], y = iy + kOff[j][1], x = ix + kOff[j][2];
-        if (z < 0 || z >= TZ || y < 0 || y >= TY || x < 0 || x >= TX)
-          dep |= (uint32_t)((M[li + kOff[j][0] * HXY + kOff[j][1] * G::HX + kOff[j][2]] >>
-                             (j ^ 1)) & 1u) << j;
-      }
-      if (dep) dirs |= out_dirs<TZ, TY, TX>(i, dep);
-    }
-  } else {
-    // the face points push into the tile
-    uint32_t n = 0;
-#pragma unroll
-    for (int q = 0; q < F::kPer; ++q) {
-      if (w + q * kWaves >= F::kSlots) continue;
-      const FaceSlot& f = kFaces<TZ, TY, TX>.s[w + q * kWaves];
-      const uint32_t nv = hl[q] >= 0 ? hv[q] + f.weight : 0u;
-      const int l = hl[q] >= 0 ? hl[q] : f.li;
-      uint32_t x[F::ND], old[F::ND];
-#pragma unroll
-      for (int k = 0; k < F::ND; ++k) x[k] = P[l + f.d[k]];
-#pragma unroll
-      for (int k = 0; k < F::ND; ++k)
-        old[k] = raise_word(&P[l + f.d[k]], (x[k] & f.keep[k]) < nv, x[k], nv);
-#pragma unroll
-      for (int k = 0; k < F::ND; ++k) list_risen(E, E.list[w][0], n, old[k], l + f.d[k], nv);
-    }
-    int rounds = 1 + push_rounds<TZ, TY, TX>(P, E, n);
-    __syncthreads();
-    if (E.over) {
-      // some raised points were not listed: passes to the end, and every
-      // neighbour tile looks
-      rounds += word_passes<TZ, TY, TX>(P, E, counters);
-      dirs = 0x7ffffffu;
-    }
-    if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)rounds);
-    // the neighbour tiles whose halo points rose
-#pragma unroll
-    for (int q = 0; q < F::kPer; ++q) {
-      if (hl[q] >= 0 && P[hl[q]] >= (kHalo | kRose)) dirs |= cell_dir<TZ, TY, TX>(hl[q]);
-    }
-#pragma unroll
-    for (int k = 0; k < G::PER; ++k) {
-      const uint32_t wd = P[li0 + k * G::kSlot];
-      if (QM && blockers) {
-        const int i = tid + k * kThreads;
-        if (om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
-      }
-      if (wd & kRose) {
-        if (QM)
-          __hip_atomic_store(sub + og[k], wd & 0xffffu, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-        else sub[og[k]] = wd & 0xffffu;
-      }
-    }
+    for (int k = 0; k < F::ND; ++k) list_risen(E, E.list[w][0], n, old[k], l + f.d[k], nv);
   }
-  // queue mode: every wave's subbins have to be out before wave 0, past the
-  // barriers below, lets the tile go (q_finish), as its next run, on whatever
-  // XCD, starts from them; a barrier alone does not wait for stores
-  if (QM) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  if (QM && blockers) {
-    const uint64_t both = block_or64((uint64_t)ups << 32 | dirs);
-    if (threadIdx.x == 0) blockers[t] = (uint32_t)(both >> 32) & ~0x3fffu;
-    return (uint32_t)both;
-  }
-  if (__ballot(dirs != 0u)) {
-    dirs = wave_reduce(dirs, OpOr{});
-    if (lane() == 0) atomicOr(&E.dirs, dirs);
-  }
+  const int rounds = 1 + push_rounds<TZ, TY, TX>(P, E, n);
   __syncthreads();
-  return E.dirs;
+  if (threadIdx.x == 0) atomicAdd(&itot[t % 64], (unsigned long long)rounds);
+  if (__builtin_expect(E.over, 0))
+    return whole_run<TZ, TY, TX, QM>(lds, box, tl, mask, sub, counters, itot, t, blockers, false);
+  // the neighbour tiles whose halo points rose
+  uint32_t dirs = 0, ups = 0;
+#pragma unroll
+  for (int q = 0; q < F::kPer; ++q) {
+    if (hl[q] >= 0 && P[hl[q]] >= (kHalo | kRose)) dirs |= cell_dir<TZ, TY, TX>(hl[q]);
+  }
+#pragma unroll
+  for (int k = 0; k < G::PER; ++k) {
+    const uint32_t wd = P[li0 + k * G::kSlot];
+    if (QM && blockers) {
+      const int i = tid + k * kThreads;
+      if (om[k] && G::on_edge(i)) ups |= out_dirs<TZ, TY, TX>(i, om[k]);
+    }
+    if (wd & kRose) {
+      if (QM)
+        __hip_atomic_store(sub + og[k], wd & 0xffffu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else sub[og[k]] = wd & 0xffffu;
+    }
+  }
+  return end_run<QM>(E, dirs, ups, blockers, t);
 }
 
 // mark_neighbours for a sweep run colour by colour: a neighbour of the later
@@ -1881,7 +2098,7 @@ __global__ __launch_bounds__(kThreads) void k_point_iter(Box box, const uint16_t
       z = (int)(p / nxy);
       y = (int)((p / nx) % (uint32_t)box.ny);
       x = (int)(p % nx);
-      const uint32_t m = mask[p];
+      const uint32_t m = box.nz == 1 ? flags_of<1>(mask[p]) : mask[p];
       const uint32_t cur = sub[p];
       uint32_t best = cur;
 #pragma unroll
