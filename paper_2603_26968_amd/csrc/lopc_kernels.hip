@@ -1655,7 +1655,8 @@ __device__ __forceinline__ uint32_t end_run(EventLds<NPT>& E, uint32_t dirs, uin
 // 2D 56; unrolled and called 87 and 100, rolled up and called 74 and 87).
 // Bound by the chain of its steps.  Against events and passes to the end: 1800
 // x 3600 fronts at bound 1e-2 2,250 -> 715 us a call, at 1e-1 8,830 -> 2,025, at
-// 1e0 19,050 -> 7,160.
+// 1e0 19,050 -> 7,160; with 32-bit subbins a chain of 2^18 points in a row
+// 1,578 -> 318 ms under host sweeps.
 template <int TZ, int TY, int TX, bool QM>
 __device__ __forceinline__ uint32_t whole_run(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
                                            const uint16_t* __restrict__ mask,
@@ -1748,6 +1749,7 @@ __device__ __forceinline__ uint32_t whole_run(RunLds<TZ, TY, TX>& lds, Box box, 
       if (p.li >= 0) P[p.li] = p.in ? load(p.g) : 0u;
     }
     __syncthreads();
+    if constexpr (TZ == 1) steps = level_run<TZ, TY, TX, true>(lds, tid, flags, level);
     // the flags of the owned and the face points
     uint16_t* const M = &lds.E.list[0][0][0];
     static_assert(sizeof(lds.E.list) >= G::H * 2, "the flags fit the event lists");

@@ -54,6 +54,18 @@ def fields():
     yield "falling 2D", -np.arange(70 * 150).reshape(70, 150) / 2.0 ** 19, 0
     yield "falling 3D", -np.arange(9 * 30 * 70).reshape(9, 30, 70) / 2.0 ** 19, 0
     yield "random 2D", rng.permutation(200 * 300).reshape(200, 300) / 2.0 ** 19, 0
+    big = wound(160, 31, 64)
+    big[big < BARRIER] -= 4  # leave room below for points of small subbins
+    small = rng.random(big.shape) < 0.1
+    mixed = np.where((big == BARRIER) & small, 90.0 + rng.random(big.shape), big)
+    yield "wound 2D, above 60,000", mixed, 60000
+    # a thin 2D field, both ways round: rows (columns) above each other in one bin
+    yield "3 x 70000", -np.arange(3 * 70000).reshape(3, 70000) / 2.0 ** 19, 60000
+    yield "70000 x 3", -np.arange(3 * 70000).reshape(70000, 3) / 2.0 ** 19, 60000
+    # planes of the wound field above each other: every neighbour direction
+    deep = np.repeat(wound(170, 31, 64)[None], 2, axis=0)
+    deep[1] -= deep[1] < BARRIER
+    yield "wound 3D, above 60,000", deep, 60000
 
 
 @pytest.mark.parametrize("dt", [np.float32, np.float64], ids=["f32", "f64"])
