@@ -72,6 +72,7 @@ int lopc_ctx_create(int hip_device, lopc_ctx** out) {
   c->sweeps_hint = 16;
   c->persist_pct = 0;
   c->sweep_hint = 4;
+  c->few_from = 3;  // the later half of the first group of all
   c->repair_mode = LOPC_REPAIR_AUTO;
   c->sweep_order = 0;
   for (int i = 0; i < kTileShapes; ++i) c->rq_per_cu[i] = c->sl_per_cu[i] = 0;
@@ -183,12 +184,21 @@ static int repair_by_sweeps(lopc_ctx* ctx, const Shape& s, const CompressLayout&
   uint64_t sweeps = 1, active = tl.ntiles;
   const uint32_t K = (uint32_t)ctx->sweep_hint;
   const size_t report = L.queue + sizeof(RepairQueue);
-  // few tiles are marked in the later half of the sweeps
+  // A sweep goes to the resident workgroups (k_repair_few) where it has marked
+  // tiles for at most a quarter of them, so that hardly any gets two; in the
+  // first group, where the marks are not known yet, from the sweep on after
+  // which that held in the context's previous call.  us a call, never / by the
+  // position in the group / up to all / up to a quarter: 512^3 float32 at bound
+  // 1e-2 2,987 / 2,898 / 2,883 / 2,887, 512^3 float64 lognormal 10,920 / 10,680 /
+  // 10,681 / 10,717, 2D 8192 x 9000 at 1e-1 (levels, 30 to 60 us a run) 14,600 /
+  // 17,640 / 15,070 / 14,500.
+  const uint32_t few = (uint32_t)(kFewWaves * ctx->num_cu), few_marks = few / 4;
+  uint64_t few_from = 1;  // after the last sweep that marked more
   for (uint32_t t = 1; t <= K; ++t) {
     Ev e = t == 1 ? ev_first(ctx, LOPC_PHASE_REPAIR) : Ev{};
     if (t == K) e.b = ev_last(ctx, LOPC_PHASE_REPAIR).b;
     HIP_CTX(ctx, launch_repair(s.box, tl, (const uint16_t*)(ws + L.mask), sub, stamp,
-                               counters, t, 2 * t > K + 1, hs, e));
+                               counters, t, (int)t >= ctx->few_from ? few : 0u, hs, e));
   }
   HIP_CTX(ctx, launch_encode(dtype, (uint32_t)s.n, ws + L.bins, sub, (uint16_t*)(ws + L.mask),
                              ws + L.tail, offs, (uint32_t*)(ws + L.parts), prm,
@@ -215,6 +225,7 @@ static int repair_by_sweeps(lopc_ctx* ctx, const Shape& s, const CompressLayout&
       if (t < next + batch) {
         ++sweeps;
         active += m;
+        if (m > few_marks) few_from = (uint64_t)t + 1;
       }
     }
     if (done) break;
@@ -237,16 +248,17 @@ static int repair_by_sweeps(lopc_ctx* ctx, const Shape& s, const CompressLayout&
       return cap >= s.n + 2 ? LOPC_E_INTERNAL : kRestartOnQueue;  // the former unreachable
     }
     batch = (uint32_t)std::min<uint64_t>(batch, cap + 1 - next);  // the last group ends at cap
-    const bool few = (uint64_t)hc[1 + (next & 63)] * 8 < tl.ntiles;
+    const uint32_t grid = hc[1 + (next & 63)] > few_marks ? 0u : few;
     for (uint32_t b = 0; b < batch; ++b)
       HIP_CTX(ctx, launch_repair(s.box, tl, (const uint16_t*)(ws + L.mask), sub, stamp,
-                                 counters, next + b, few, hs,
+                                 counters, next + b, grid, hs,
                                  b + 1 == batch ? ev_last(ctx, LOPC_PHASE_REPAIR) : Ev{}));
     HIP_CTX(ctx, hipMemcpyAsync(ctx->h_prm, ws, report, hipMemcpyDeviceToHost, hs));
     HIP_CTX(ctx, hipStreamSynchronize(hs));
   }
   // the next call starts with as many sweeps as this one needed, plus one
   ctx->sweep_hint = (int)std::min<uint64_t>(16, std::max<uint64_t>(2, sweeps));
+  ctx->few_from = (int)std::min<uint64_t>(few_from, INT32_MAX);
   if (next > 1) {
     // the gated encoder did not run: encode now
     HIP_CTX(ctx, launch_encode(dtype, (uint32_t)s.n, ws + L.bins, sub,

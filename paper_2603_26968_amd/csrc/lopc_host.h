@@ -48,6 +48,7 @@ struct lopc_ctx {
   hipEvent_t ev[2 * LOPC_PHASES];  // per phase: first kernel's start, last kernel's end
   double ms[LOPC_PHASES];
   int sweep_hint;      // single field: repair sweeps enqueued before the first read
+  int few_from;        // single field: first of its last sweeps that all mark few tiles
   int repair_mode;     // single field: LOPC_REPAIR_HYBRID, _QUEUE or _SWEEPS
   int sweep_order;     // single field, host-driven sweeps: LOPC_OPT_SWEEP_ORDER
   int rq_per_cu[lopc::kTileShapes];  // resident repair-queue workgroups per CU, per tile shape

@@ -296,17 +296,19 @@ hipError_t launch_report(const Params* prm, const RepairQueue* q, uint64_t* d_si
 // saves.
 constexpr uint32_t kColourMinTiles = 32768;
 
-// Waves per SIMD, and so workgroups (of four waves) per CU, of a batch sweep.
-constexpr int kRepairWaves = 5;
+// Waves per SIMD, and so workgroups (of four waves) per CU, of a batch sweep and
+// of a single field's sweep over few marked tiles (k_repair_few).
+constexpr int kRepairWaves = 5, kFewWaves = 6;
 
 // One host-driven sweep: the tiles marked for `sweep`; with t.coloured,
 // in two launches by tile colour (checkerboard), so that a tile of the
 // second colour sees the changes of its face and corner neighbours in the
-// same sweep.  few: expect few marked tiles (only how they are handed out
-// depends on it).  Ev: start of the first launch, end of the last.
+// same sweep.  few > 0: few marked tiles are expected, `few` workgroups look
+// for them and run them in turn (only how tiles are handed out depends on it).
+// Ev: start of the first launch, end of the last.
 hipError_t launch_repair(Box box, Tiling t, const uint16_t* mask,
                          uint32_t* sub, uint32_t* stamp, uint32_t* counters,
-                         uint32_t sweep, bool few, hipStream_t s, Ev ev = {});
+                         uint32_t sweep, uint32_t few, hipStream_t s, Ev ev = {});
 // Point worklists (LOPC_REPAIR_POINTS): list every point with flags for
 // iteration 0 (its length in ring[0]); one iteration `it` over the list win
 // (length ring[it % 64]) appending to wout (length ring[(it + 1) % 64]).

@@ -437,9 +437,6 @@ constexpr uint32_t kEventShare = NPT / 16;
 constexpr uint32_t kEventCost = 36;
 // Events of a round up to which each gets a lane per neighbour.
 constexpr uint32_t kNarrow = 32;
-// Workgroups of a single-field sweep that expects few marked tiles: the six of
-// each of 256 CUs that k_repair_few's registers leave room for.
-constexpr uint32_t kFewGrid = 1536;
 
 // Event lists of a tile run (LDS indices of raised points; two alternating
 // lists per wave) and its block-wide words.
@@ -1972,12 +1969,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
 // workgroup looks at every gridDim.x-th from its own on, all marks in one read,
 // and runs the marked ones in turn.  With a workgroup per tile a sweep takes the
 // time to start them all and read their marks: 30 us for 65,536 tiles of a
-// colour, whatever is marked.  Where most are marked that is the better: a
+// colour, whatever is marked.  Where many are marked that is the better: a
 // workgroup starts as another ends, and its registers leave room for eight
-// (512^3 float64, 24 launches: the later half this way 10.96 -> 10.63 ms a
-// call, all of them 12.35 ms).
+// (512^3 float64 lognormal: all sweeps this way 12.35 ms a call, none 10.9).
 template <int TZ, int TY, int TX>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_repair_few(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kFewWaves, 8))) void k_repair_few(
     Box box, Tiling tl, const uint16_t* __restrict__ mask,
     uint32_t* __restrict__ sub, uint32_t* stamp, uint32_t* counters,
     uint32_t sweep, uint32_t colour, uint32_t n) {
@@ -2519,15 +2515,17 @@ int repair_q_blocks_per_cu(int sid) {
 }
 
 hipError_t launch_repair(Box box, Tiling t, const uint16_t* mask, uint32_t* sub,
-                         uint32_t* stamp, uint32_t* counters, uint32_t sweep, bool few,
+                         uint32_t* stamp, uint32_t* counters, uint32_t sweep, uint32_t few,
                          hipStream_t s, Ev ev) {
   // both colours, or every tile at once; the events bracket the sweep
   const bool col2 = t.coloured != 0;
   const uint32_t n =
       col2 ? (uint32_t)t.ntz * (uint32_t)t.nty * (uint32_t)((t.ntx + 1) / 2) : t.ntiles;
   const uint32_t nl = col2 ? 2 : 1;
-  // tiles a workgroup looks at where few are marked, and the workgroups then
-  const uint32_t per = few ? std::min(64u, (n + kFewGrid - 1) / kFewGrid) : 1u;
+  // tiles a workgroup looks at where few are marked, and the workgroups then;
+  // below eight each starting one per tile costs less than two marked tiles in
+  // a row (2D 1800 x 3600, 3,219 tiles, bound 1e-1: 1,860 against 2,000 us)
+  const uint32_t per = few && n >= 8 * few ? std::min(64u, (n + few - 1) / few) : 1u;
   for (uint32_t l = 0; l < nl; ++l) {
     Ev e{l == 0 ? ev.a : nullptr, l == nl - 1 ? ev.b : nullptr};
     if (per > 1) {
