@@ -37,20 +37,17 @@ constexpr uint32_t kMaxRounds = kMaxUnits / 64;  // 32
 
 // Scratch of the decoder's unit-parallel RZE stages.
 struct Scratch {
-  uint8_t lv0[kMaxUnits + 16] __attribute__((aligned(16)));  // level-1 bitmap
+  // the bitmap levels from level 1 up (level 0 is expanded in registers)
   uint8_t lv1[256 + 16] __attribute__((aligned(16)));
   uint8_t lv2[32 + 16] __attribute__((aligned(16)));
   uint8_t lv3[16] __attribute__((aligned(16)));
-  uint32_t rpre[kMaxRounds + 1];  // per-round totals, then exclusive prefix
-  uint32_t scan[kCW + 1];
-  uint32_t nkept[4];
-  uint64_t orv[kCW];
-  uint64_t scan64[kCW + 1];
+  uint32_t rpre[kMaxRounds];  // items of each round
+  uint32_t nkept[2];
   uint64_t planes;
 };
 
 __device__ __forceinline__ uint8_t* lvl(Scratch& sc, int l) {
-  return l == 0 ? sc.lv0 : (l == 1 ? sc.lv1 : (l == 2 ? sc.lv2 : sc.lv3));
+  return l == 1 ? sc.lv1 : (l == 2 ? sc.lv2 : sc.lv3);
 }
 // Bitmap bytes of RZE level l for `items` items: ceil(items / 8^(l+1)) (each
 // level is the bitmap of the one below; nested ceilings compose).  Computed

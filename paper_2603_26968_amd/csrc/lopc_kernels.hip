@@ -193,19 +193,6 @@ __device__ __forceinline__ uint32_t out_dirs(int i, uint32_t bits) {
 }
 
 // OR of v over the workgroup (every thread gets it)
-__device__ __forceinline__ uint32_t block_or32(uint32_t v) {
-  __shared__ uint32_t w[kWaves];
-  v = wave_reduce(v, OpOr{});
-  if (lane() == 0) w[wave()] = v;
-  __syncthreads();
-  uint32_t r = 0;
-#pragma unroll
-  for (int q = 0; q < kWaves; ++q) r |= w[q];
-  __syncthreads();
-  return r;
-}
-
-// OR of v over the workgroup (every thread gets it)
 __device__ __forceinline__ uint64_t block_or64(uint64_t v) {
   __shared__ uint64_t w[kWaves];
   v = wave_reduce(v, OpOr{});
