@@ -34,7 +34,7 @@ EXPORTS = ("lopc_ctx_create", "lopc_ctx_destroy", "lopc_compress_bound",
            "lopc_ctx_last_header", "lopc_batch_workspace_size", "lopc_compress_batch",
            "lopc_decompress_batch", "lopc_ctx_last_batch", "lopc_ctx_set_option", "lopc_ctx_get_option",
            "lopc_ctx_last_batch_headers", "lopc_batch_autotune", "lopc_verify",
-           "lopc_verify_workspace_size", "lopc_decompress_static")
+           "lopc_verify_workspace_size", "lopc_decompress_static", "lopc_batch_read_headers")
 LOPC_OPT_BATCH_GRAPH, LOPC_OPT_GRAPH_SWEEPS, LOPC_OPT_PERSIST_PCT, LOPC_OPT_REPAIR = 1, 2, 3, 4
 LOPC_OPT_TILE_3D, LOPC_OPT_TILE_2D, LOPC_OPT_SWEEP_ORDER = 5, 6, 7
 # the repair tile shapes behind LOPC_OPT_TILE_2D / _3D values (z x y x x)
@@ -151,6 +151,7 @@ def load() -> ctypes.CDLL:
     L.lopc_batch_workspace_size.argtypes = [vp, ci, ci, jp, szp]
     L.lopc_batch_workspace_size.restype = ci
     L.lopc_batch_read_headers.argtypes = [ci, vp, jp]
+    L.lopc_batch_read_headers.restype = ci
     L.lopc_compress_batch.argtypes = [vp, ci, jp, vp, sz, vp, ctypes.POINTER(BatchStats)]
     L.lopc_compress_batch.restype = ci
     L.lopc_decompress_batch.argtypes = [vp, ci, jp, vp, sz, vp]
@@ -592,7 +593,8 @@ def _compress_jobs(fields, error_bounds, modes, out, ctx):
     for i, x in enumerate(fields):
         d = x.shape
         _JOB.pack_into(jobs, i * size, x.data_ptr(), 0, base + offs[i], caps[i], codes[i], len(d),
-                       d[0], d[1], d[2] if len(d) == 3 else 0, float(ebs[i]), _mode(mds[i]))
+                       d[0], d[1], d[2] if len(d) == 3 else 0, float(ebs[i]),
+                       ctypes.c_int(_mode(mds[i])).value)  # a C int, as in single calls
     return jobs, out, offs, ctx, dev
 
 
