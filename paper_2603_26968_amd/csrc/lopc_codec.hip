@@ -953,10 +953,11 @@ __global__ __launch_bounds__(kThreads) void k_place(const uint32_t* parts, const
 
 // The same without the offsets, for at most kPlaceChunks chunks: a wave per
 // record, and each workgroup sums the sizes of the records before its four
-// (two chunks per 16-byte load).  Saves the one-workgroup scan, 4.7 us of every
-// call; its reads grow with the square of the chunks: 16 MB from the L2s
-// at 4096 (256^3 binary32: 12.5 against 14 us; 1583 chunks: 5.6 against 9.9 us).
-constexpr uint32_t kPlaceChunks = 4096;
+// (two chunks per 16-byte load).  Saves the one-workgroup scan; its reads grow
+// with the square of the chunks, and beyond 16,384 they cost more than the scan.
+// Encoder and placement, with / without the scan: 4,096 chunks 75.9 / 74.8 us,
+// 8,192 140.0 / 137.1, 16,384 262.7 / 259.6, 32,768 523.0 / 528.4.
+constexpr uint32_t kPlaceChunks = 16384;
 __global__ __launch_bounds__(kThreads) void k_place_few(const uint32_t* parts, uint32_t nch,
                                                         RecordSlots S, Params* prm,
                                                         uint8_t* stream, uint64_t cap,
@@ -965,7 +966,8 @@ __global__ __launch_bounds__(kThreads) void k_place_few(const uint32_t* parts, u
   __shared__ uint32_t sh[kThreads / 64];
   constexpr uint32_t kWaves = kThreads / 64;
   const uint32_t c0 = blockIdx.x * kWaves, w = (uint32_t)__builtin_amdgcn_readfirstlane(wave());
-  uint32_t sum = 0;  // below 4096 records of at most 40 KiB: 32 bits
+  uint32_t sum = 0;  // at most kPlaceChunks records of at most 40 KiB: 32 bits
+  static_assert((uint64_t)kPlaceChunks * (kRecordTailBytes + 8192) < (1ull << 32), "offsets in 32 bits");
   for (uint32_t i = threadIdx.x; i < c0 / 2; i += kThreads) {
     const uint4 a = ((const uint4*)parts)[i];
     sum += record_size(a.x, a.y) + record_size(a.z, a.w);
