@@ -1155,7 +1155,7 @@ __device__ bool q_claim(const QueueRef& Q, uint32_t t, const TileCoord& c, const
   return true;
 }
 
-// End of a run of tile t (wave 0 of its block, whose waves have each released
+// End of a run of tile t (wave 0 of its block, whose waves have each waited for
 // their subbin stores before the block's last barrier): list the neighbour
 // tiles in `dirs` (27-bit set, see out_dirs), stop running, publish the tiles
 // parked on t, and stop counting the run as pending.
@@ -1616,8 +1616,11 @@ __device__ __forceinline__ uint32_t end_run(EventLds<NPT>& E, uint32_t dirs, uin
                                             uint32_t* blockers, uint32_t t) {
   // queue mode: every wave's subbins have to be out before wave 0, past the
   // barriers below, lets the tile go (q_finish), as its next run, on whatever
-  // XCD, starts from them; a barrier alone does not wait for stores
-  if (QM) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  // XCD, starts from them; a barrier alone does not wait for stores.  They are
+  // agent-scope stores, which write through, so waiting for them is enough: a
+  // release fence would write the whole L2 back (queue alone, 128^3 float64
+  // lognormal 35.9 -> 31.0 ms, 128^3 float32 turbulence 1.25 -> 1.02 ms)
+  if (QM) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (QM && blockers) {
     const uint64_t both = block_or64((uint64_t)ups << 32 | dirs);
     if (threadIdx.x == 0) blockers[t] = (uint32_t)(both >> 32) & ~0x3fffu;
