@@ -1,13 +1,12 @@
 // lopc_kernels.hip -- gfx950 kernels of liblopc.so (LOPC, arXiv 2603.26968).
 //
-// Wave64 throughout: bit planes and zero bitmaps are built with __ballot,
-// compaction offsets with mbcnt and block scans, chunk offsets of the
-// compressed stream with a decoupled look-back over a ticket-ordered chunk
-// queue.  No MFMA: nothing here is a dense contraction.
+// Range, error bound, first tile pass and subbin repair (lopc_codec.hip has the
+// chunk encoder and decoder).  Wave64 throughout: order flags from comparison
+// masks joined on the scalar side, list places from ballots and mbcnt.  No
+// MFMA: nothing here is a dense contraction.
 //
 // Paper map: error bound and quantizer Sec. IV-A; neighbour order flags and
-// subbin raising Alg. 1 / Alg. 2 / Sec. IV-B; lossless stages Sec. III-B and
-// Sec. IV-C; decoding rule Sec. IV-E.
+// subbin raising Alg. 1 / Alg. 2 / Sec. IV-B.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
@@ -259,7 +258,6 @@ __device__ __forceinline__ TileCoord tile_coord(uint32_t t, const Tiling& tl) {
   return c;
 }
 
-// local fixed point of the tile (masks of the owned points in registers)
 // the relaxation-iteration slots of the single-field counters block
 __device__ __forceinline__ unsigned long long* relax_total(uint32_t* counters) {
   return (unsigned long long*)(counters + kRelaxWord);
@@ -491,7 +489,7 @@ __device__ __forceinline__ void list_risen(EventLds<NPT>& E, uint16_t* list, uin
 // small ones.  Against passes over all points until none rises: the 24 sweep
 // launches on a 512^3 float64 lognormal field 8.3 -> 6.1 ms (vector
 // instructions of the first 2971 -> 1790 per wave, of the sixth 1298 -> 550),
-// 2D 1800 x 3600 float32 sweeps 304 -> 190 us.
+// 2D 1800 x 3600 float32 sweeps 300 -> 170 us (145 with the runs by levels).
 template <int TZ, int TY, int TX>
 __device__ __forceinline__ int push_rounds(uint32_t* P, EventLds<TZ * TY * TX>& E, uint32_t n) {
   using G = TileGeom<TZ, TY, TX>;
@@ -638,8 +636,8 @@ __device__ __forceinline__ int word_passes(uint32_t* P, EventLds<TZ * TY * TX>& 
 // point with at most three lower neighbours reads them at precomputed offsets
 // (walk_code: three loads issued back to back).  Other waves visit their slots
 // and read every stencil neighbour at once, masked.  Once a pass raises at
-// most a quarter of the points (and some wave is not listed), those points
-// become the first event list.  On a lognormal field (91% of the points in
+// most a sixteenth of the points (kEventShare; and some wave is not listed), those
+// points become the first event list.  On a lognormal field (91% of the points in
 // one bin) the passes raise 77, 54, 40, 31, 25, 19, 15, 12% ... of the points,
 // fifteen in all: the later ones cost far less as events.  Adds the pass count
 // to one of 64 statistics slots itot[t % 64].  PK: the slots' masks are spread
@@ -1505,20 +1503,6 @@ __attribute__((amdgpu_waves_per_eu(kTile0Waves<K, TZ, TY, TX>, 8))) void k_tile0
 }
 
 
-// Later sweeps: tiles marked for this sweep reload their halo and relax.
-// One sweep of tile t if it is marked for it.  Returns (block-uniform) the
-// neighbour tiles holding a point that would rise from what changed in this
-// tile (0 if the tile did not run).
-// A run pushes the halo points into the tile (what changed since the tile's
-// last run can only have come from there), then each wave runs event rounds
-// from the points it raised.
-// QM (queue mode): the tile was taken from the repair queue, and other
-// workgroups change subbins while it runs, so subbins are read and written
-// as relaxed atomics at agent scope (coherent across the XCDs' L2 caches).
-// LOOP: the tile is known to be marked, and the kernel runs several in turn.
-// With `blockers` given, thread 0 stores there the higher-index
-// neighbour tiles holding a same-bin lower neighbour of one of the tile's
-// points (the tiles its run depends on; bits 14..26 of the 27-direction set).
 // LDS of a run, handed in by the kernel (one buffer where it runs 2D and 3D
 // tiles).
 template <int TZ, int TY, int TX>
@@ -1781,6 +1765,21 @@ __device__ __forceinline__ uint32_t whole_run(RunLds<TZ, TY, TX>& lds, Box box, 
   return end_run<QM>(lds.E, dirs, ups, blockers, t);
 }
 
+// One sweep of tile t if it is marked for it: a run reloads the subbins and the
+// flags of the tile and its halo, raises what follows and writes what rose.
+// Returns (block-uniform) the neighbour tiles holding a point that would rise
+// from what changed in this tile (0 if the tile did not run).
+// A run pushes the halo points into the tile (what changed since the tile's
+// last run can only have come from there), then each wave runs event rounds
+// from the points it raised; with too many events, or subbins that do not fit
+// an LDS word, it goes over the whole tile (whole_run).
+// QM (queue mode): the tile was taken from the repair queue, and other
+// workgroups change subbins while it runs, so subbins are read and written
+// as relaxed atomics at agent scope (coherent across the XCDs' L2 caches).
+// LOOP: the tile is known to be marked, and the kernel runs several in turn.
+// With `blockers` given, thread 0 stores there the higher-index
+// neighbour tiles holding a same-bin lower neighbour of one of the tile's
+// points (the tiles its run depends on; bits 14..26 of the 27-direction set).
 template <int TZ, int TY, int TX, bool QM = false, bool LOOP = false>
 __device__ __forceinline__ uint32_t repair_body(RunLds<TZ, TY, TX>& lds, Box box, Tiling tl,
                             const uint16_t* __restrict__ mask, uint32_t* __restrict__ sub,
@@ -2007,18 +2006,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kFewWa
   }
 }
 
-// Device-driven repair of a single field: a persistent grid takes tiles from
-// the repair queue until nothing is listed or running.  A tile run reloads
-// the halo, relaxes, writes what changed, releases it and lists the
-// neighbour tiles that depend on a changed boundary point; then the run
-// stops counting as pending.  Subbins only rise and stay below the least
-// fixed point, so the result does not depend on the order of the runs.
 // One sweep over a work list: a persistent grid takes the listed tiles
 // through a cursor; each reloads its halo, relaxes, writes what changed and
 // lists the neighbour tiles that depend on a changed boundary point for the
-// next sweep.  An empty list costs one atomic per workgroup.  The run is
-// out of line for the reason given at repair_run below.
-
+// next sweep.  An empty list costs one atomic per workgroup.  The run is out
+// of line, like repair_run below: the kernel takes 103 registers (3D; 116 in
+// 2D), inlined and held to 6 waves per SIMD 72 (80), which gains on the largest
+// fields and loses more on others (512^3 float64 18.9 -> 17.8 ms a call, 128^3
+// 0.62 -> 0.77).
 template <int TZ, int TY, int TX>
 __device__ __noinline__ uint32_t sweep_run(Box box, Tiling tl, const uint16_t* __restrict__ mask,
                                            uint32_t* __restrict__ sub, const uint32_t* stamp,
@@ -2143,10 +2138,16 @@ __global__ __launch_bounds__(kThreads) void k_seed_queue(const uint32_t* counter
     q_push(Q, in[i], sweep);
 }
 
-// One queued tile run, kept out of line: inlined into the worker loop, the
-// per-thread halo offsets of the body were hoisted out of the loop and kept
-// live across it (180 VGPRs instead of 67).  Its LDS arrays are its own, so
-// their accesses still compile to ds_* instructions.
+// Device-driven repair of a single field: a persistent grid takes tiles from
+// the repair queue until nothing is listed or running.  A tile run reloads
+// the halo, relaxes, writes what changed, waits until that is out and lists the
+// neighbour tiles that depend on a changed boundary point; then the run
+// stops counting as pending.  Subbins only rise and stay below the least
+// fixed point, so the result does not depend on the order of the runs.
+
+// One queued tile run, kept out of line, so that what the body derives from the
+// thread's place is not hoisted out of the worker loop and held across it.  Its
+// LDS arrays are its own, so their accesses still compile to ds_* instructions.
 template <int TZ, int TY, int TX>
 __device__ __noinline__ uint32_t repair_run(Box box, Tiling tl, const uint16_t* __restrict__ mask,
                                             uint32_t* __restrict__ sub, uint32_t* counters,
