@@ -112,7 +112,7 @@ def measured_traffic(workload, phase):
         return None
     h = hashlib.sha256()
     for f in ("lopc_codec.hip", "lopc_kernels.hip", "lopc_device.h", "lopc_internal.h",
-              "lopc_numeric.h"):
+              "lopc_numeric.h", "lopc_tile.h"):
         h.update(open(os.path.join(ROOT, "paper_2603_26968_amd", "csrc", f), "rb").read())
     src = h.hexdigest()[:16]
     for line in open(path):
